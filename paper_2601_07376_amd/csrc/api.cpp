@@ -282,11 +282,6 @@ lora_status make_plan(const lora_table* t, int32_t n, const int32_t* idx,
   p->d.mrb = reinterpret_cast<int4*>(b + L.mrb);
   p->d.srec = reinterpret_cast<lora::SmallRec*>(b + L.srec);
   p->d.seg_ids = reinterpret_cast<int32_t*>(b + L.seg_ids);
-  p->d.ch_hist = reinterpret_cast<int32_t*>(b + L.ch_hist);
-  p->d.ch_mhist = reinterpret_cast<int32_t*>(b + L.ch_mhist);
-  p->d.ch_runs = reinterpret_cast<int32_t*>(b + L.ch_runs);
-  p->d.ch_flags = reinterpret_cast<int32_t*>(b + L.ch_flags);
-  p->d.minfo = reinterpret_cast<int32_t*>(b + L.minfo);
   p->d.chunks = L.chunks;
   p->r_max = 0;
   p->rank8 = true;
@@ -380,12 +375,6 @@ PlanLayout plan_layout(int32_t n, int32_t S) {
   L.srec = o;        o += al256((size_t)L.srec_max * sizeof(SmallRec));
   L.seg_ids = o;     o += al256(nn * 4);
   L.chunks = (n > PLAN_THREADS && n <= PLAN_MULTI_MAX) ? (n + PLAN_THREADS - 1) / PLAN_THREADS : 0;
-  const size_t ch = (size_t)L.chunks;
-  L.ch_hist = o;     o += al256(ch * S * 4);
-  L.ch_mhist = o;    o += al256(ch * S * 4);
-  L.ch_runs = o;     o += al256(ch * 4);
-  L.ch_flags = o;    o += al256(ch * 4);
-  L.minfo = o;       o += al256(ch ? nn * 4 : 0);
   L.total = o;
   return L;
 }

@@ -45,8 +45,8 @@ constexpr int IDS_MAX_ROWS = 1024;  // most rows of a plan-free (lora_apply_ids)
 constexpr int MRB_ROWS = 64;     // trainable rows per gradient row block
 constexpr int PLAN_THREADS = 1024;
 constexpr int PLAN_WAVES = PLAN_THREADS / 64;
-// batches of (PLAN_THREADS, PLAN_MULTI_MAX] rows are grouped by two launches over
-// chunks of PLAN_THREADS rows; longer ones by one workgroup
+// batches of (PLAN_THREADS, PLAN_MULTI_MAX] rows are grouped by one workgroup per
+// chunk of PLAN_THREADS rows; longer ones by one workgroup
 constexpr int PLAN_MULTI_MAX = 65536;
 
 // One small-group entry as the fused kernel reads it: everything a workgroup
@@ -69,7 +69,7 @@ static_assert(sizeof(SmallRec) == 128, "small-group record layout");
 struct PlanLayout {
   size_t hdr, counts, offsets, perm, run_start, run_end, run_adapter;
   size_t m_counts, m_offsets, m_perm, m_blk, rb, mrb, srec, seg_ids;
-  size_t ch_hist, ch_mhist, ch_runs, ch_flags, minfo, total;   // chunked grouping
+  size_t total;
   int32_t rb_max, mrb_max, srec_max, chunks;
 };
 
@@ -89,13 +89,8 @@ struct PlanDev {
   int4* rb;     // {adapter, first index into perm, rows, 0}
   int4* mrb;    // {adapter, first index into m_perm, rows, 0}
   SmallRec* srec;  // small-group records, in the order of the small rb entries
-  int32_t* seg_ids;   // packed ids (one workgroup), or per-row id and rank (chunked)
-  int32_t* ch_hist;   // chunked grouping: [chunk][adapter] row counts
-  int32_t* ch_mhist;  //   ... of trainable rows
-  int32_t* ch_runs;   //   [chunk] run starts
-  int32_t* ch_flags;  //   [chunk] data flags
-  int32_t* minfo;     //   per-row trainable id and rank
-  int32_t chunks;     //   chunks of PLAN_THREADS rows (0: not chunked)
+  int32_t* seg_ids;   // packed ids (one-workgroup grouping)
+  int32_t chunks;     // chunks of PLAN_THREADS rows (0: one workgroup)
 };
 
 // Device address of this GPU's fixed scratch array (lora_apply_noalloc),

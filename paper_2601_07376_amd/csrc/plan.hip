@@ -11,6 +11,8 @@
 // in row order and scatters each row to its cursor.  Rows of one adapter inside
 // a 64-row chunk are found with ballots over the bits of the id, so a chunk
 // needs no atomics: the lowest lane of each id group owns that group's cursor.
+#include <type_traits>
+
 #include "device_common.h"
 #include "lora_internal.h"
 
@@ -655,52 +657,152 @@ __global__ __launch_bounds__(T) void plan_small_kernel(PlanLaunch a) {
 
 
 // ---------------------------------------------------------------------------
-// Batches of (PLAN_THREADS, PLAN_MULTI_MAX] rows: two launches over chunks of
-// PLAN_THREADS rows, one workgroup per chunk.
-//   count:   ids validated; each row's rank among its chunk's rows of the same
-//            adapter (and under the mask); per-chunk adapter histograms, run
-//            starts and data flags.
-//   scatter: each chunk adds the histograms of the chunks before it (and of
-//            all chunks, for the adapter offsets), then its rows scatter to
-//            perm, m_perm, their record slot and their run; the first chunk
-//            writes counts, offsets, entry lists and the header.
+// Batches of (PLAN_THREADS, PLAN_MULTI_MAX] rows: one launch over chunks of
+// PLAN_THREADS rows, one workgroup per chunk, and no workgroup waits for
+// another.  Each workgroup counts the whole batch itself (rows per adapter
+// before its chunk and after it, run starts before it), groups its own chunk's
+// rows by ballots, and so knows the final position of each of them; the entry
+// lists are dealt over the workgroups.
+//
+// What bounds it: latency (a few hundred KB of ids in the L2).  The counting
+// costs each workgroup one read of the ids, all requests in flight at once, and
+// LDS counters (one add per wave where its 64 rows share an adapter, as in
+// segments); a segment batch without a mask counts its segments instead of
+// its rows.  Two dependent launches (histograms per chunk, then a scatter that
+// walked the chunks' histograms one load after another) took, replayed from a
+// graph over 32 segments and 256 slots, 9.5 us at 1025 rows, 12.1 at 8192, 14.4
+// at 16384 and 32 at 65536; this one 8.4, 7.8, 7.6 and 7.6 (segments), and for
+// random ids 10.1 -> 9.4, 11.3 -> 9.5, 12.9 -> 10.5 and 26.7 -> 21.0.  In a
+// stream the launch that went is worth another 1-2 us.
 // ---------------------------------------------------------------------------
+// Four consecutive ids or mask bytes from any address the caller may give
+// (ids are 4-byte aligned, masks are not aligned): the structs tell the
+// compiler so.
+struct __attribute__((packed, aligned(4))) Ids4 {
+  int32_t v[4];
+};
+struct __attribute__((packed, aligned(1))) Mask4 {
+  uint32_t v;
+};
+
 template <bool MASKED, bool SEG>
-__global__ __launch_bounds__(PLAN_THREADS) void plan_count_kernel(PlanLaunch a) {
+__global__ __launch_bounds__(PLAN_THREADS) void plan_multi_kernel(PlanLaunch a) {
   __shared__ int s_rank[LORA_MAX_SLOTS];
-  __shared__ unsigned short s_wc[LORA_MAX_SLOTS * PLAN_WAVES];    // [adapter][wave]
-  __shared__ unsigned short s_wcm[MASKED ? LORA_MAX_SLOTS * PLAN_WAVES : 1];
+  // own chunk: rows (low half) and trainable rows (high half) of [adapter][wave]
+  __shared__ uint32_t s_wc[LORA_MAX_SLOTS * PLAN_WAVES];
+  // rows before / after the chunk (under a mask: trainable rows in the upper
+  // half, so that a row is one LDS add)
+  typedef typename std::conditional<MASKED, unsigned long long, unsigned>::type Cnt;
+  __shared__ Cnt s_pre[LORA_MAX_SLOTS], s_post[LORA_MAX_SLOTS];
+  __shared__ int s_base[LORA_MAX_SLOTS], s_mbase[MASKED ? LORA_MAX_SLOTS : 1];
+  __shared__ uint32_t s_own[LORA_MAX_SLOTS];
+  __shared__ int s_off[LORA_MAX_SLOTS], s_cnt[LORA_MAX_SLOTS], s_sbase[LORA_MAX_SLOTS];
   __shared__ int s_seg[SEG ? SEG_STAGE : 1];
-  __shared__ int s_elast[PLAN_WAVES];
-  __shared__ int s_nst;
+  __shared__ int s_efirst[PLAN_WAVES], s_elast[PLAN_WAVES];
+  __shared__ int s_w[8][PLAN_WAVES];
+  __shared__ int s_runs[2];          // run starts before the chunk, in other chunks
   __shared__ unsigned s_flags;
 
   const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
   const int n = a.n, S = a.num_slots, ns = a.num_segs;
-  const int c = blockIdx.x, t = c * PLAN_THREADS + tid;
   const PlanDev& d = a.d;
+  const int C = d.chunks, c = blockIdx.x;
+  const int t0 = c * PLAN_THREADS, t = t0 + tid, t1 = min(n, t0 + PLAN_THREADS);
 
-  if (tid == 0) {
-    s_flags = 0u;
-    s_nst = 0;
-  }
-  int raw = -1, rawp = -1, mk = 1;
+  // The other chunks' rows, four consecutive ones per thread and batch.  The
+  // first UB batches are requested with the first loads of the kernel.
+  constexpr int UB = 4;
+  Ids4 xr[UB];
+  int xp[UB];                          // (lane 0) the id before the wave's first row
+  Mask4 xm[UB];
+  auto fetch = [&](int b0) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int r0 = ((b0 + u) * PLAN_THREADS + tid) * 4;
+      xp[u] = -1;
+      xm[u].v = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xr[u].v[q] = -1;
+      if (r0 + 4 <= n) {
+        if (!SEG) xr[u] = *reinterpret_cast<const Ids4*>(a.idx + r0);
+        if (MASKED) xm[u] = *reinterpret_cast<const Mask4*>(a.mask + r0);
+      } else {
+        for (int q = 0; q < 4; ++q) {
+          if (r0 + q >= n) break;
+          if (!SEG) xr[u].v[q] = a.idx[r0 + q];
+          if (MASKED) xm[u].v |= (uint32_t)a.mask[r0 + q] << (8 * q);
+        }
+      }
+      if (!SEG && lane == 0 && r0 > 0 && r0 < n) xp[u] = a.idx[r0 - 1];
+    }
+  };
+
+  // ---- 1. loads: own rows and their neighbours outside the chunk, segments,
+  // slot ranks, the first rows of the other chunks; counters cleared
+  int raw = -1, rawb = -1, mk = 1;      // rawb: the row before (thread 0) / after (last thread)
+  const int tb = tid == 0 ? t0 - 1 : tid == PLAN_THREADS - 1 ? t0 + PLAN_THREADS : -1;
   if (!SEG) {
     if (t < n) raw = a.idx[t];
-    if (tid == 0 && t > 0) rawp = a.idx[t - 1];
+    if (tb >= 0 && tb < n) rawb = a.idx[tb];
   } else {
     for (int i = tid; i <= ns; i += PLAN_THREADS) s_seg[i] = a.seg_offsets[i];
     for (int i = tid; i < ns; i += PLAN_THREADS) s_seg[ns + 1 + i] = a.seg_adapter[i];
   }
   if (MASKED && t < n) mk = a.mask[t];
-  for (int i = tid; i < S * PLAN_WAVES; i += PLAN_THREADS) {
-    s_wc[i] = 0;
-    if (MASKED) s_wcm[i] = 0;
+  SlotMeta my{};
+  if (tid < S) my = a.meta[tid];
+  if (!SEG || MASKED) fetch(0);
+  for (int i = tid; i < S * PLAN_WAVES; i += PLAN_THREADS) s_wc[i] = 0u;
+  if (tid < S) {
+    s_rank[tid] = my.rank;
+    s_pre[tid] = s_post[tid] = 0;
   }
-  if (tid < S) s_rank[tid] = a.meta[tid].rank;
-  __syncthreads();
+  if (tid == 0) {
+    s_flags = 0u;
+    s_runs[0] = s_runs[1] = 0;
+  }
+  const bool some_empty = __syncthreads_or(tid < S && my.rank <= 0 ? 1 : 0) != 0;
 
   uint32_t flags = 0u;
+  auto validate = [&](int v, bool report) {
+    if (v < -1 || v >= S) {
+      if (report) flags |= LORA_DATA_BAD_ID;
+      return -1;
+    }
+    if (some_empty && v >= 0 && s_rank[v] <= 0) {
+      if (report) flags |= LORA_DATA_EMPTY_SLOT;
+      return -1;
+    }
+    return v;
+  };
+  auto seg_at = [&](int row) {
+    int lo = 0, hi = ns;             // s_seg[lo] <= row < s_seg[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (s_seg[mid] <= row) lo = mid;
+      else hi = mid;
+    }
+    return lo;
+  };
+  // Up to 63 segments: lane i holds segment i's first row and adapter, and the
+  // segment of a row that is the same in the whole wave is one ballot away (a
+  // binary search waits for an LDS read per step).  A wave whose rows [r0, r1)
+  // lie in one segment takes its adapter for all of them; else its lanes walk
+  // on from the first row's segment.
+  bool segs_ok = true;
+  const bool few = SEG && ns < 64;
+  const int so_l = few && lane <= ns ? s_seg[lane] : INT32_MAX;
+  const int sa_l = few && lane < ns ? s_seg[ns + 1 + lane] : -1;
+  auto wave_seg = [&](int r0, int r1, int& sg, int& id) {
+    sg = __popcll(__ballot(so_l <= r0)) - 1;
+    if (sg < 0 || lane_value(so_l, sg + 1) < r1) return false;
+    id = lane_value(sa_l, sg);
+    return true;
+  };
+  auto walk = [&](int sg, int row) {
+    while (sg + 1 < ns && s_seg[sg + 1] <= row) ++sg;
+    return sg;
+  };
   if (SEG) {
     bool bad = false;
     for (int i = tid; i <= ns; i += PLAN_THREADS) {
@@ -711,216 +813,233 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_count_kernel(PlanLaunch a) 
     }
     if (__syncthreads_or(bad ? 1 : 0)) {
       flags |= LORA_DATA_BAD_SEGMENTS;
+      segs_ok = false;
     } else {
-      auto seg_of = [&](int row) {
-        int lo = 0, hi = ns;             // s_seg[lo] <= row < s_seg[hi]
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (s_seg[mid] <= row) lo = mid;
-          else hi = mid;
-        }
-        return s_seg[ns + 1 + lo];
-      };
-      if (t < n) raw = seg_of(t);
-      if (tid == 0 && t > 0) rawp = seg_of(t - 1);
+      const int rw = t0 + w * 64;
+      const int rb = w == 0 ? t0 - 1 : w == PLAN_WAVES - 1 ? t0 + PLAN_THREADS : -1;
+      int sg;
+      if (few) {
+        if (rw < n && !wave_seg(rw, min(n, rw + 64), sg, raw) && t < n) raw = s_seg[ns + 1 + walk(max(sg, 0), t)];
+        if (rb >= 0 && rb < n) wave_seg(rb, rb + 1, sg, rawb);
+      } else {
+        if (t < n) raw = s_seg[ns + 1 + seg_at(t)];
+        if (rb >= 0 && rb < n) rawb = s_seg[ns + 1 + seg_at(rb)];
+      }
     }
   }
-  auto validate = [&](int v, bool report) {
-    if (v < -1 || v >= S) {
-      if (report) flags |= LORA_DATA_BAD_ID;
-      return -1;
-    }
-    if (v >= 0 && s_rank[v] <= 0) {
-      if (report) flags |= LORA_DATA_EMPTY_SLOT;
-      return -1;
-    }
-    return v;
-  };
+
+  // ---- 2. own chunk: per-wave group sizes by ballots
   const int e = t < n ? validate(raw, true) : -1;
-  const int ep0 = (tid == 0 && t > 0) ? validate(rawp, false) : -1;   // previous chunk's last row
+  const int eb = (tb >= 0 && tb < n) ? validate(rawb, false) : -1;
   const int em = (MASKED && !mk) ? -1 : e;
   const int nbits = 32 - __clz(S);
   const uint64_t lt = lanemask_lt();
   const uint64_t peers = match_peers(e + 1, nbits);
   const int rank_in = __popcll(peers & lt);
-  if (e >= 0 && rank_in == 0) s_wc[e * PLAN_WAVES + w] = (unsigned short)__popcll(peers);
-  int mrank_in = 0;
-  if (MASKED) {
-    const uint64_t mpeers = match_peers(em + 1, nbits);
-    mrank_in = __popcll(mpeers & lt);
-    if (em >= 0 && mrank_in == 0) s_wcm[em * PLAN_WAVES + w] = (unsigned short)__popcll(mpeers);
-  }
+  uint64_t mpeers = peers;
+  if (MASKED) mpeers &= __ballot(em >= 0);
+  const int mrank_in = __popcll(mpeers & lt);
+  if (e >= 0 && rank_in == 0)
+    s_wc[e * PLAN_WAVES + w] = (uint32_t)__popcll(peers) | ((uint32_t)__popcll(mpeers) << 16);
+  if (lane == 0) s_efirst[w] = e;
   if (lane == 63) s_elast[w] = e;
+
+  // ---- 3. the other chunks: rows per adapter before and after this one, run
+  // starts before it and in all of them
+  int rpre = 0, roth = 0;
+  auto both = [](uint32_t rows, uint32_t train) {
+    return MASKED ? (Cnt)(((unsigned long long)train << 32) | rows) : (Cnt)rows;
+  };
+  // rows (and, above them, trainable rows) of adapter ee >= 0 added by every
+  // lane with k != 0; at most 256 per wave and half, so 16 bits hold each
+  auto count = [&](Cnt* cnt, int ee, int rows, int train) {
+    const int k = rows | (train << 16);
+    const uint64_t act = __ballot(k != 0);
+    if (act == 0) return;
+    const int lead = __ffsll((unsigned long long)act) - 1;
+    const int e0 = __builtin_amdgcn_readlane(ee, lead);
+    if (__ballot(k != 0 && ee != e0) == 0) {
+      const uint32_t tot = (uint32_t)lane_value(wave_incl_scan(k), 63);
+      if (lane == lead) atomicAdd(&cnt[e0], both(tot & 0xffffu, tot >> 16));
+    } else if (k != 0) {
+      atomicAdd(&cnt[ee], both(rows, train));
+    }
+  };
+  if (SEG && segs_ok) {
+    for (int i = tid; i < ns; i += PLAN_THREADS) {
+      const int o0 = s_seg[i], o1 = s_seg[i + 1];
+      if (o1 <= o0) continue;
+      const int se = validate(s_seg[ns + 1 + i], true);
+      if (se < 0) continue;
+      if (!(o0 >= t0 && o0 < t1)) {
+        const int sj = o0 <= 0 ? -1 : s_seg[i - 1] < o0 ? i - 1 : seg_at(o0 - 1);   // segment of the row before
+        const int sp = sj >= 0 ? validate(s_seg[ns + 1 + sj], false) : -1;
+        if (sp != se) {
+          ++roth;
+          rpre += o0 < t0 ? 1 : 0;
+        }
+      }
+      const int before = min(o1, t0) - o0, after = o1 - max(o0, t0 + PLAN_THREADS);
+      if (before > 0) atomicAdd(&s_pre[se], both(before, 0));
+      if (after > 0) atomicAdd(&s_post[se], both(after, 0));
+    }
+  }
+  if (!SEG || MASKED) {
+    const int nb = (n + 4 * PLAN_THREADS - 1) / (4 * PLAN_THREADS);
+    for (int b0 = 0; b0 < nb; b0 += UB) {
+      if (b0 > 0) fetch(b0);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        // (a wave's 256 rows lie in one chunk)
+        const int r0 = ((b0 + u) * PLAN_THREADS + tid) * 4;
+        const int cc = uni(r0 / PLAN_THREADS);
+        if (cc >= C || cc == c) continue;
+        Cnt* const cnt = cc < c ? s_pre : s_post;
+        int id[4];
+        if (SEG) {
+          const int rw = uni(r0);
+          int e0 = -1, sg = -1;
+          if (segs_ok && few && wave_seg(rw, min(n, rw + 256), sg, e0)) {
+            e0 = validate(e0, false);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) id[q] = e0;      // (rows past n have no mask)
+          } else {
+            const bool in = segs_ok && r0 < n;
+            if (in) sg = few ? walk(max(sg, 0), r0) : seg_at(r0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              if (in && q > 0) sg = walk(sg, min(r0 + q, n - 1));
+              id[q] = in && r0 + q < n ? validate(s_seg[ns + 1 + sg], false) : -1;
+            }
+          }
+        } else {
+          const int prev = lane_prev(xr[u].v[3], xp[u]);
+          int st = 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            id[q] = validate(xr[u].v[q], true);
+            // (equal raw ids are equal ids; a live id differs from any other)
+            st += id[q] >= 0 && xr[u].v[q] != (q ? xr[u].v[q - 1] : prev) ? 1 : 0;
+          }
+          roth += st;
+          rpre += cc < c ? st : 0;
+        }
+        const bool same = id[0] == id[1] && id[1] == id[2] && id[2] == id[3];
+        if (__ballot(!same) == 0) {
+          const uint32_t m = xm[u].v;
+          const int k = !MASKED ? 0 : ((m & 0xffu) != 0) + ((m & 0xff00u) != 0) +
+                                      ((m & 0xff0000u) != 0) + ((m & 0xff000000u) != 0);
+          count(cnt, id[0], !SEG && id[0] >= 0 ? 4 : 0, id[0] >= 0 ? k : 0);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t tr = MASKED && ((xm[u].v >> (8 * q)) & 0xffu) ? 1 : 0;
+            if (id[q] >= 0 && (!SEG || tr)) atomicAdd(&cnt[id[q]], both(SEG ? 0 : 1, tr));
+          }
+        }
+      }
+    }
+  }
+  roth = lane_value(wave_incl_scan(roth), 63);
+  rpre = lane_value(wave_incl_scan(rpre), 63);
+  if (lane == 0 && roth) {
+    atomicAdd(&s_runs[1], roth);
+    atomicAdd(&s_runs[0], rpre);
+  }
+  if (flags) atomicOr(&s_flags, flags);
   __syncthreads();
 
-  // per adapter: exclusive prefix over waves, chunk total to the histogram
+  // ---- 4. own chunk: exclusive prefix over waves, per adapter (both halves at
+  // once: at most PLAN_THREADS rows, so nothing carries)
   for (int k0 = 0; k0 < S * PLAN_WAVES; k0 += PLAN_THREADS) {
     const int k = k0 + tid;
     const bool act = k < S * PLAN_WAVES;
     const int v = act ? (int)s_wc[k] : 0;
     const int incl = row_incl_scan(v);
     if (act) {
-      s_wc[k] = (unsigned short)(incl - v);
-      if ((k & 15) == 15) d.ch_hist[c * S + (k >> 4)] = incl;
-    }
-    if (MASKED) {
-      const int vm = act ? (int)s_wcm[k] : 0;
-      const int im = row_incl_scan(vm);
-      if (act) {
-        s_wcm[k] = (unsigned short)(im - vm);
-        if ((k & 15) == 15) d.ch_mhist[c * S + (k >> 4)] = im;
-      }
+      s_wc[k] = (uint32_t)(incl - v);
+      if ((k & 15) == 15) s_own[k >> 4] = (uint32_t)incl;
     }
   }
-  const int ep = lane_prev(e, w > 0 ? s_elast[w - 1] : ep0);
-  const uint64_t stb = __ballot(e >= 0 && ep != e);
-  if (lane == 0 && stb) atomicAdd(&s_nst, __popcll(stb));
-  __syncthreads();
-
-  if (t < n) {
-    d.seg_ids[t] = e >= 0 ? (e + 1) | (((int)s_wc[e * PLAN_WAVES + w] + rank_in) << 16) : 0;
-    if (MASKED)
-      d.minfo[t] = em >= 0 ? (em + 1) | (((int)s_wcm[em * PLAN_WAVES + w] + mrank_in) << 16) : 0;
-  }
-  if (flags) atomicOr(&s_flags, flags);
-  __syncthreads();
-  if (tid == 0) {
-    d.ch_runs[c] = s_nst;
-    d.ch_flags[c] = (int32_t)s_flags;
-  }
-}
-
-template <bool MASKED>
-__global__ __launch_bounds__(PLAN_THREADS) void plan_scatter_kernel(PlanLaunch a) {
-  __shared__ int s_base[LORA_MAX_SLOTS];      // adapter offset + its rows in earlier chunks
-  __shared__ int s_mbase[MASKED ? LORA_MAX_SLOTS : 1];
-  __shared__ int s_off[LORA_MAX_SLOTS];
-  __shared__ int s_cnt[LORA_MAX_SLOTS];
-  __shared__ int s_sbase[LORA_MAX_SLOTS];
-  __shared__ int s_w[8][PLAN_WAVES];
-  __shared__ int s_misc[4];
-
-  const int tid = threadIdx.x;
-  const int n = a.n, S = a.num_slots;
-  const PlanDev& d = a.d;
-  const int C = d.chunks, c = blockIdx.x, t = c * PLAN_THREADS + tid;
-  const int t0 = c * PLAN_THREADS;
-
-  // this chunk's rows (and their neighbours, for the run boundaries)
-  const int info = t < n ? d.seg_ids[t] : 0;
-  const int infop = (t > 0 && t - 1 < n) ? d.seg_ids[t - 1] : 0;
-  const int infon = t + 1 < n ? d.seg_ids[t + 1] : 0;
-  const int minf = (MASKED && t < n) ? d.minfo[t] : 0;
-
-  // per adapter: rows in all chunks and in the chunks before this one
-  int cnt = 0, pre = 0, mcnt = 0, mpre = 0;
-  if (tid < S) {
-    for (int cc = 0; cc < C; ++cc) {
-      const int v = d.ch_hist[cc * S + tid];
-      cnt += v;
-      pre += cc < c ? v : 0;
-      if (MASKED) {
-        const int vm = d.ch_mhist[cc * S + tid];
-        mcnt += vm;
-        mpre += cc < c ? vm : 0;
-      }
-    }
-  }
-  if (!MASKED) {
-    mcnt = cnt;
-    mpre = pre;
-  }
-  if (tid == 0) {
-    int rpre = 0, rtot = 0;
-    uint32_t fl = 0u;
-    for (int cc = 0; cc < C; ++cc) {
-      const int r = d.ch_runs[cc];
-      rtot += r;
-      rpre += cc < c ? r : 0;
-      fl |= (uint32_t)d.ch_flags[cc];
-    }
-    // a run that crosses into this chunk ends here, not before it
-    const int eb = t0 > 0 ? (d.seg_ids[t0 - 1] & 0xffff) - 1 : -1;
-    const int ef = (d.seg_ids[t0] & 0xffff) - 1;
-    s_misc[0] = rpre;
-    s_misc[1] = rtot;
-    s_misc[2] = (int)fl;
-    s_misc[3] = rpre - ((eb >= 0 && eb == ef) ? 1 : 0);
-  }
-
-  const int e = (info & 0xffff) - 1;
-  const int ep = t > 0 ? (infop & 0xffff) - 1 : -1;
-  const int en = t + 1 < n ? (infon & 0xffff) - 1 : -1;
+  const int ep = lane_prev(e, w > 0 ? s_elast[w - 1] : eb);
+  const int en = lane_next(e, w + 1 < PLAN_WAVES ? s_efirst[w + 1] : eb);
   const bool st = e >= 0 && ep != e;
   const bool ed = e >= 0 && en != e;
+  // (the first row's predecessor, in thread 0): a run that crosses into this
+  // chunk ends here, not before it
+  const int cross = (tid == 0 && e >= 0 && eb == e) ? 1 : 0;
+  __syncthreads();
 
+  // ---- 5. offsets, entry positions and run indices in one scan
   const bool live = tid < S;
+  const unsigned long long cpre = live ? s_pre[tid] : 0, cpost = live ? s_post[tid] : 0;
+  const uint32_t own = live ? s_own[tid] : 0u;
+  const int pre = (int)(uint32_t)cpre;
+  const int cnt = pre + (int)(own & 0xffffu) + (int)(uint32_t)cpost;
+  const int mpre = MASKED ? (int)(cpre >> 32) : pre;
+  const int mcnt = MASKED ? mpre + (int)(own >> 16) + (int)(cpost >> 32) : cnt;
   const bool small = live && cnt > 0 && cnt <= a.small_max;
   const bool large = live && cnt > a.small_max;
-  const int nbc = large ? (cnt + RB_ROWS - 1) / RB_ROWS : 0;
-  const int nbf = large ? (cnt + RB_FINE - 1) / RB_FINE : 0;
+  const int rbr = a.fine != 0 ? RB_FINE : RB_ROWS;    // chosen on the host (the launches follow it)
+  const int nbl = large ? (cnt + rbr - 1) / rbr : 0;
   const int nbs = small ? (cnt + SMALL_ROWS - 1) / SMALL_ROWS : 0;
   const int nbm = live ? (mcnt + MRB_ROWS - 1) / MRB_ROWS : 0;
-  int v[8] = {cnt, mcnt, nbc, nbs, nbm, st ? 1 : 0, ed ? 1 : 0, nbf};
+  int v[8] = {cnt, mcnt, nbl, nbs, nbm, st ? 1 : 0, ed ? 1 : 0, cross};
   int tot[8];
-  block_scan_n<8>(v, tot, s_w);            // (barriers inside: s_misc is visible after it)
-  const int off = v[0], moff = v[1], ps = v[3], pm = v[4];
-  // block size of the whole batch, chosen on the host (the launches follow it)
-  const bool fine = a.fine != 0;
-  const int rbr = fine ? RB_FINE : RB_ROWS, nbl = fine ? nbf : nbc, pl = fine ? v[7] : v[2];
-  const int tot_l = fine ? tot[7] : tot[2];
+  block_scan_n<8>(v, tot, s_w);
+  const int off = v[0], moff = v[1], pl = v[2], ps = v[3], pm = v[4];
+  const int tot_l = tot[2];
   if (live) {
-    s_base[tid] = off + pre;
-    if (MASKED) s_mbase[tid] = moff + mpre;
     s_off[tid] = off;
     s_cnt[tid] = cnt;
     s_sbase[tid] = small ? ps : -1;
-  }
-  if (c == 0) {
-    if (live) {
-      const SlotMeta my = a.meta[tid];
+    s_base[tid] = off + pre;          // first positions of this chunk's rows
+    if (MASKED) s_mbase[tid] = moff + mpre;
+    if (c == 0) {
       d.counts[tid] = cnt;
       d.offsets[tid] = off;
       d.m_counts[tid] = mcnt;
       d.m_offsets[tid] = moff;
       d.m_blk[tid] = pm;
-      for (int i = 0; i < nbl; ++i)
-        d.rb[pl + i] = make_int4(tid, off + i * rbr, min(rbr, cnt - i * rbr), 0);
-      for (int i = 0; i < nbs; ++i) {
-        const int rows = min(SMALL_ROWS, cnt - i * SMALL_ROWS);
-        d.rb[tot_l + ps + i] = make_int4(tid, off + i * SMALL_ROWS, rows, 1);
-        SmallRec* r = d.srec + ps + i;
-        r->A = my.A;
-        r->B = my.B;
-        r->rows = rows;
-        r->rank = my.rank;
-        r->scale = my.scale;
-        r->adapter = tid;
-      }
-      for (int i = 0; i < nbm; ++i)
-        d.mrb[pm + i] = make_int4(tid, moff + i * MRB_ROWS, min(MRB_ROWS, mcnt - i * MRB_ROWS), 0);
     }
-    if (tid == 0) {
-      d.offsets[S] = tot[0];
-      d.m_offsets[S] = tot[1];
-      int32_t* h = d.hdr;
-      h[HDR_FLAGS] = s_misc[2];
-      h[HDR_NACT] = tot[0];
-      h[HDR_NRUNS] = s_misc[1];
-      h[HDR_MNACT] = tot[1];
-      h[HDR_NRB_LARGE] = tot_l;
-      h[HDR_NRB_TOTAL] = tot_l + tot[3];
-      h[HDR_RB_ROWS] = rbr;
-      h[HDR_NMRB] = tot[4];
-      h[HDR_NSMALL] = tot[3];
+    // entry i of each list is written by workgroup i mod C
+    for (int i = c; i < nbl; i += C)
+      d.rb[pl + i] = make_int4(tid, off + i * rbr, min(rbr, cnt - i * rbr), 0);
+    for (int i = c; i < nbs; i += C) {
+      const int rows = min(SMALL_ROWS, cnt - i * SMALL_ROWS);
+      d.rb[tot_l + ps + i] = make_int4(tid, off + i * SMALL_ROWS, rows, 1);
+      // the record's first 32 bytes as two 16-byte stores
+      int4* r4 = reinterpret_cast<int4*>(d.srec + ps + i);
+      const uint64_t pa = reinterpret_cast<uint64_t>(my.A), pb = reinterpret_cast<uint64_t>(my.B);
+      r4[0] = make_int4((int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)(uint32_t)pb,
+                        (int)(uint32_t)(pb >> 32));
+      r4[1] = make_int4(rows, my.rank, __float_as_int(my.scale), tid);
     }
+    for (int i = c; i < nbm; i += C)
+      d.mrb[pm + i] = make_int4(tid, moff + i * MRB_ROWS, min(MRB_ROWS, mcnt - i * MRB_ROWS), 0);
+  }
+  if (c == 0 && tid == 0) {
+    d.offsets[S] = tot[0];
+    d.m_offsets[S] = tot[1];
+    int32_t* h = d.hdr;
+    h[HDR_FLAGS] = (int32_t)s_flags;
+    h[HDR_NACT] = tot[0];
+    h[HDR_NRUNS] = s_runs[1] + tot[5];
+    h[HDR_MNACT] = tot[1];
+    h[HDR_NRB_LARGE] = tot_l;
+    h[HDR_NRB_TOTAL] = tot_l + tot[3];
+    h[HDR_RB_ROWS] = rbr;
+    h[HDR_NMRB] = tot[4];
+    h[HDR_NSMALL] = tot[3];
   }
   __syncthreads();
 
+  // ---- 6. scatter
   // (every index below is < n or < the record count by construction; the
   // guards only keep a broken invariant from writing outside the arrays)
+  const uint32_t wc = e >= 0 ? s_wc[e * PLAN_WAVES + w] : 0u;
   if (e >= 0) {
-    const int pos = s_base[e] + (info >> 16);
+    const int pos = s_base[e] + (int)(wc & 0xffffu) + rank_in;
     if ((unsigned)pos < (unsigned)n) {
       d.perm[pos] = t;
       if (!MASKED) d.m_perm[pos] = t;
@@ -936,14 +1055,11 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_scatter_kernel(PlanLaunch a
         for (int jj = j + 1; jj < SMALL_ROWS; ++jj) r->row[jj] = t;
     }
   }
-  if (MASKED) {
-    const int em = (minf & 0xffff) - 1;
-    if (em >= 0) {
-      const int pos = s_mbase[em] + (minf >> 16);
-      if ((unsigned)pos < (unsigned)n) d.m_perm[pos] = t;
-    }
+  if (MASKED && em >= 0) {
+    const int pos = s_mbase[em] + (int)(wc >> 16) + mrank_in;
+    if ((unsigned)pos < (unsigned)n) d.m_perm[pos] = t;
   }
-  const int ks = s_misc[0] + v[5], ke = s_misc[3] + v[6];
+  const int ks = s_runs[0] + v[5], ke = s_runs[0] - tot[7] + v[6];
   if (st && (unsigned)ks < (unsigned)n) {
     d.run_start[ks] = t;
     d.run_adapter[ks] = e;
@@ -976,14 +1092,10 @@ hipError_t launch_plan(const PlanLaunch& a, hipStream_t s) {
   if (a.d.chunks > 0 && (!seg || 2 * a.num_segs + 1 <= SEG_STAGE)) {
     const dim3 g(a.d.chunks), b(PLAN_THREADS);
     const bool m = a.mask != nullptr;
-    if (m && seg) hipLaunchKernelGGL((plan_count_kernel<true, true>), g, b, 0, s, a);
-    else if (m) hipLaunchKernelGGL((plan_count_kernel<true, false>), g, b, 0, s, a);
-    else if (seg) hipLaunchKernelGGL((plan_count_kernel<false, true>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((plan_count_kernel<false, false>), g, b, 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (m) hipLaunchKernelGGL((plan_scatter_kernel<true>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((plan_scatter_kernel<false>), g, b, 0, s, a);
+    if (m && seg) hipLaunchKernelGGL((plan_multi_kernel<true, true>), g, b, 0, s, a);
+    else if (m) hipLaunchKernelGGL((plan_multi_kernel<true, false>), g, b, 0, s, a);
+    else if (seg) hipLaunchKernelGGL((plan_multi_kernel<false, true>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((plan_multi_kernel<false, false>), g, b, 0, s, a);
     return hipGetLastError();
   }
   const bool pk_lds = a.n <= LDS_ROWS;

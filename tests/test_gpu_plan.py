@@ -85,6 +85,48 @@ def test_plan_fuzz(name):
     assert got["data_flags"] == 0
 
 
+@pytest.mark.parametrize("n", [1025, 2047, 4095, 4097, 16385, 65533])
+@pytest.mark.parametrize("masked", [False, True])
+def test_plan_chunked_unaligned(n, masked):
+    """Batches grouped in chunks of 1024 rows: ids and masks at addresses that
+    are not 16-byte aligned, bad ids and empty slots in other chunks, long and
+    short runs; the same rows as segments (empty ones among them)."""
+    say(f"plan chunked n={n} masked={masked}")
+    r = np.random.default_rng(n)
+    S = 37
+    ranks = np.full(S, 8)
+    ranks[[3, 30]] = 0
+    lens = np.where(r.random(n) < 0.97, r.integers(0, 4, n), r.integers(0, 300, n))
+    k = int(np.searchsorted(np.cumsum(lens), n)) + 1
+    lens = lens[:k]
+    lens[-1] -= int(lens.sum()) - n
+    ad = r.integers(-2, S + 1, k)
+    idx = np.repeat(ad, lens)
+    mask = r.integers(0, 2, n) if masked else None
+    table = L.Table(S, 8, 8, device=DEV)
+    w = torch.zeros(8, 8, dtype=torch.bfloat16, device=DEV)
+    for a in np.nonzero(ranks)[0]:
+        table.set(int(a), w, w, 1.0)
+    table.upload()
+    buf = torch.full((n + 5,), 99, dtype=torch.int32, device=DEV)
+    buf[1:n + 1] = torch.from_numpy(idx.astype(np.int32)).to(DEV)
+    mbuf = torch.full((n + 5,), 1, dtype=torch.uint8, device=DEV)
+    if masked:
+        mbuf[3:n + 3] = torch.from_numpy(mask.astype(np.uint8)).to(DEV)
+    m_t = mbuf[3:n + 3] if masked else None
+    ref = oracle.canonical_plan(idx, S, mask=mask, ranks=ranks)
+    got = L.Plan(table, idx=buf[1:n + 1], mask=m_t).export()
+    compare_plan(got, ref)
+    flags = (L.LORA_DATA_BAD_ID if np.any((idx < -1) | (idx >= S)) else 0) | \
+            (L.LORA_DATA_EMPTY_SLOT if np.isin(idx, [3, 30]).any() else 0)
+    assert got["data_flags"] == flags
+    segs = dict(seg_offsets=torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV),
+                seg_adapter=torch.from_numpy(ad.astype(np.int32)).to(DEV))
+    got = L.Plan(table, n=n, mask=m_t, **segs).export()
+    compare_plan(got, ref)
+    assert got["data_flags"] == flags
+
+
 def test_plan_bad_ids_and_empty_slots():
     say("plan bad ids")
     rng = np.random.default_rng(5)
