@@ -550,8 +550,10 @@ __global__ __launch_bounds__(256) void dadb_kernel(GradArgs g) {
   __shared__ __align__(16) uint16_t s_p[2][2 * NT * 16 * DT_ROWS];   // [hl][j] columns
   __shared__ int s_rows[DT_WIN];
   const int nbB = (g.d_out + CT - 1) / CT, nbA = (g.d_in + CT - 1) / CT, nbt = nbB + nbA;
-  const XcdRange xr = xcd_range(g.slot_count * nbt);
-  for (int tile = xr.first; tile < xr.end; tile += xr.step) {
+  // tiles dealt round-robin over the XCDs: a slot with many rows is then read by
+  // all eight of them (one slot per XCD left one XCD streaming the largest
+  // slot alone: 4705 trainable rows of 6 slots, 5120 wide, 68 -> 56 us)
+  for (int tile = blockIdx.x; tile < g.slot_count * nbt; tile += gridDim.x) {
     const int sl = tile / nbt, c = tile - sl * nbt;
     const int r = uni(g.meta[g.slot_base + sl].rank);
     if (r <= 0) continue;
