@@ -204,8 +204,8 @@ typedef struct lora_policy {
   int32_t small_chunks;  /* output-column chunks per small group, 1..16 (-1: ceil(d_out / 1024)) */
   int32_t fork;          /* mixed batch in lora_apply: 0 = one stream, 1 = small groups on the
                             second stream (-1: when n < 64 x num_slots) */
-  int32_t grad_splits;   /* most d-slices of the gradient's first stage, 1..8
-                            (-1: ceil(min(d_in, d_out) / 512)) */
+  int32_t grad_splits;   /* 1..8 or -1; kept for callers that set it: the gradient's first
+                            stage takes the whole of d_in and d_out per unit */
   int32_t block_rows;    /* rows per block of the large groups, 64 or 256 (-1: 64 when
                             n < 12288, else 256); only that size's kernels are launched */
 } lora_policy;
@@ -377,10 +377,10 @@ lora_status lora_grad_x(const lora_plan* p, const void* dY, lora_dtype dy_dtype,
 
 /* Both gradients of one backward step in one call: lora_grad's dA_a / dB_a
  * and lora_grad_x's dX, with exactly their results (same kernels, same
- * arguments and semantics as the two calls).  The input gradient runs on a
- * library-owned second stream of the stream's device, forked from and joined
- * back into `stream` with events, beside the adapter gradients; both read the
- * plan and dY as they are when the call is made.  ws:
+ * arguments and semantics as the two calls).  G = dY B_a is computed once for
+ * both; then dX is written on a library-owned second stream of the stream's
+ * device, forked from and joined back into `stream` with events, beside the
+ * adapter gradients' reduction over rows.  ws:
  * lora_backward_workspace_bytes(p) bytes, 16-byte aligned.  Needs bfloat16 dY
  * and weights (the input gradient's matrix-core path).  Errors: those of the
  * two calls, all checked before anything is enqueued. */

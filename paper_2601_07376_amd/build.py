@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblora_mi355x.so")
 DEBUG_LIB = os.path.join(HERE, "liblora_mi355x_debug.so")
-SOURCES = ["plan.hip", "fwd_mfma.hip", "fwd_valu.hip", "grad.hip", "adamw.hip", "losses.hip",
+SOURCES = ["plan.hip", "fwd_mfma.hip", "fwd_valu.hip", "grad.hip", "rowprod.hip", "adamw.hip", "losses.hip",
            "noalloc.hip", "linear.hip", "calib.hip", "api.cpp"]
 ARCH = "gfx950"
 

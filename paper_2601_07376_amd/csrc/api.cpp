@@ -31,6 +31,7 @@ struct lora_plan {
   lora::PlanDev d;
   int32_t r_max;        // largest live rank when the plan was built
   bool rank8;           // every live rank is a multiple of 8
+  bool rank4;           // ... of 4
   int32_t small_max;    // groups of <= small_max rows use the fused small-group kernel
   bool fine;            // large groups in blocks of RB_FINE rows (else RB_ROWS)
   lora_policy pol;      // path selection of the ops on this plan (-1 fields: library choice)
@@ -71,14 +72,6 @@ size_t dsize(lora_dtype d) { return d == LORA_BF16 ? 2 : 4; }
 int32_t small_chunks_policy(const lora_plan* p) {
   if (p->pol.small_chunks > 0) return p->pol.small_chunks;
   return std::max(1, std::min(16, (p->table->d_out + 1023) / 1024));
-}
-
-// Most d-slices of the gradient's first stage (the kernel uses fewer when
-// there are enough row blocks to fill the chip).
-int32_t grad_splits_policy(const lora_plan* p) {
-  if (p->pol.grad_splits > 0) return std::min(p->pol.grad_splits, lora::GRAD_SPLITS_MAX);
-  const int32_t d = std::min(p->table->d_in, p->table->d_out);
-  return std::max(1, std::min(lora::GRAD_SPLITS_MAX, (d + 511) / 512));   // slices of >= 512
 }
 
 // Each field is -1 (the library's choice) or inside its documented range.
@@ -284,11 +277,12 @@ lora_status make_plan(const lora_table* t, int32_t n, const int32_t* idx,
   p->d.seg_ids = reinterpret_cast<int32_t*>(b + L.seg_ids);
   p->d.chunks = L.chunks;
   p->r_max = 0;
-  p->rank8 = true;
+  p->rank8 = p->rank4 = true;
   for (const auto& s : t->host) {
     if (s.rank <= 0) continue;
     p->r_max = std::max(p->r_max, s.rank);
     p->rank8 = p->rank8 && (s.rank % 8 == 0);
+    p->rank4 = p->rank4 && (s.rank % 4 == 0);
   }
   p->pol = pol;
   p->small_max = pol.small_max >= 0 ? pol.small_max : lora::small_max_policy(n, t->num_slots);
@@ -337,14 +331,14 @@ int32_t small_max_policy(int32_t n, int32_t S) {
 // host, so only the grouped kernels of that block size are launched.
 bool fine_policy(int32_t n) { return (int64_t)n < (int64_t)FINE_BELOW * RB_ROWS; }
 
-// Gradient workspace: fp32 partial planes (two per d-slice) and the summed bf16
-// hi / lo planes.
+// Gradient workspace: fp32 planes of the vector path, bf16 hi / lo planes of the
+// matrix-core path.
 GradLayout grad_layout(int32_t mrb_ub, int32_t r_max) {
   GradLayout G{};
   const size_t r_pad = (size_t)(std::max(r_max, 1) + 15) / 16 * 16;
   const size_t p_stride = (size_t)mrb_ub * MRB_ROWS;
   size_t o = 0;
-  G.partial = o; o += al256(2 * GRAD_SPLITS_MAX * r_pad * p_stride * 4);
+  G.partial = o; o += al256(2 * r_pad * p_stride * 4);
   G.fin = o;     o += al256(2 * 2 * r_pad * p_stride * 2);
   G.total = o;
   return G;
@@ -1119,10 +1113,15 @@ size_t lora_grad_workspace_bytes(const lora_plan* p) {
   return lora::grad_layout(ub_mrb(p), p->r_max).total;
 }
 
-lora_status lora_grad(const lora_plan* p, const void* X, lora_dtype x_dtype, int64_t ldx,
-                      const void* dY, lora_dtype dy_dtype, int64_t lddy, const float* H_saved,
-                      int64_t ldh, float* const* dA, float* const* dB, int32_t accumulate,
-                      void* ws, size_t ws_bytes, void* stream) {
+}  // extern "C"
+
+namespace {
+
+// lora_grad's checks, and its launch description
+lora_status grad_setup(const lora_plan* p, const void* X, lora_dtype x_dtype, int64_t ldx,
+                       const void* dY, lora_dtype dy_dtype, int64_t lddy, const float* H_saved,
+                       int64_t ldh, float* const* dA, float* const* dB, int32_t accumulate,
+                       void* ws, size_t ws_bytes, lora::GradLaunch& g) {
   lora_status st = check_plan(p);
   if (st != LORA_OK) return st;
   const lora_table* t = p->table;
@@ -1151,8 +1150,7 @@ lora_status lora_grad(const lora_plan* p, const void* X, lora_dtype x_dtype, int
     if ((st = d.check()) != LORA_OK) return st;
   }
 
-  const bool mfma = x_dtype == LORA_BF16 && t->w_dtype == LORA_BF16;
-  lora::GradLaunch g{};
+  g = lora::GradLaunch{};
   g.o = op_base(p);
   g.o.rb = p->d.mrb;
   g.o.rb_ub = ub_mrb(p);
@@ -1175,22 +1173,64 @@ lora_status lora_grad(const lora_plan* p, const void* X, lora_dtype x_dtype, int
   char* wsb = static_cast<char*>(ws);
   g.hg = reinterpret_cast<float*>(wsb + GL.partial);
   g.fin = reinterpret_cast<uint16_t*>(wsb + GL.fin);
-  g.k_splits = mfma ? grad_splits_policy(p) : 1;
   g.p_stride = ub_mrb(p) * lora::MRB_ROWS;
   g.r_pad = (std::max(p->r_max, 1) + 15) / 16 * 16;
+  g.rank4 = p->rank4;
+  return LORA_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+lora_status lora_grad(const lora_plan* p, const void* X, lora_dtype x_dtype, int64_t ldx,
+                      const void* dY, lora_dtype dy_dtype, int64_t lddy, const float* H_saved,
+                      int64_t ldh, float* const* dA, float* const* dB, int32_t accumulate,
+                      void* ws, size_t ws_bytes, void* stream) {
+  lora::GradLaunch g;
+  const lora_status st = grad_setup(p, X, x_dtype, ldx, dY, dy_dtype, lddy, H_saved, ldh, dA, dB,
+                                    accumulate, ws, ws_bytes, g);
+  if (st != LORA_OK) return st;
+  const lora_dtype wd = p->table->w_dtype;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // n = 0 still runs: slots with no trainable row must receive zeros.
-  hipError_t e = mfma ? lora::launch_grad_mfma(g, s)
-                      : lora::launch_grad_valu(g, x_dtype, t->w_dtype, s);
+  hipError_t e;
+  if (x_dtype == LORA_BF16 && wd == LORA_BF16) {
+    e = lora::launch_grad_hg_mfma(g, nullptr, 0, s);
+    if (e == hipSuccess) e = lora::launch_grad_dadb_mfma(g, s);
+  } else {
+    e = lora::launch_grad_valu(g, x_dtype, wd, s);
+  }
   if (e != hipSuccess) return hip_fail(e, "gradient launch");
   return ok();
 }
 
 // ---- input gradient ----------------------------------------------------------
 
+}  // extern "C"
+
+namespace {
+// the expand over the plan's masked blocks that writes dX
+lora::OpLaunch grad_x_launch(const lora_plan* p) {
+  lora::OpLaunch o = op_base(p);
+  o.d_in = p->table->d_out;
+  o.d_out = p->table->d_in;          // the expand writes dX rows
+  o.rb = p->d.mrb;
+  o.perm = p->d.m_perm;
+  o.count_word = lora::HDR_NMRB;
+  o.first_word = -1;
+  o.rb_ub = ub_mrb(p);
+  o.fine_ub = ub_mrb(p);
+  return o;
+}
+}  // namespace
+
+extern "C" {
+
 size_t lora_grad_x_workspace_bytes(const lora_plan* p) {
   if (p == nullptr) return 0;
-  return apply_h_bytes(p);   // SHRINK_KS_MAX fp32 planes [n, pad8(r_max)]
+  // G, float32 [n, pad8(r_max)]
+  return al256((size_t)std::max(p->n, 1) * ((std::max(p->r_max, 1) + 7) / 8 * 8) * 4);
 }
 
 lora_status lora_grad_x(const lora_plan* p, const void* dY, lora_dtype dy_dtype, int64_t lddy,
@@ -1218,19 +1258,30 @@ lora_status lora_grad_x(const lora_plan* p, const void* dY, lora_dtype dy_dtype,
     if ((st = d.check()) != LORA_OK) return st;
   }
   if (p->n == 0) return ok();
-  lora::OpLaunch o = op_base(p);
-  o.d_in = t->d_out;                 // the shrink reads dY rows
-  o.d_out = t->d_in;                 // the expand writes dX rows
-  o.rb = p->d.mrb;
-  o.perm = p->d.m_perm;
-  o.count_word = lora::HDR_NMRB;
-  o.first_word = -1;
-  o.rb_ub = ub_mrb(p);
-  o.fine_ub = ub_mrb(p);
-  const int64_t ldh = (std::max(p->r_max, 1) + 7) / 8 * 8;
-  const int64_t plane = (int64_t)(al256((size_t)std::max(p->n, 1) * ldh * 4) / 4);
-  hipError_t e = lora::launch_grad_x_mfma(o, dY, lddy, static_cast<float*>(ws), ldh, plane, dX,
-                                          dx_dtype, lddx, static_cast<hipStream_t>(stream));
+  const int64_t ldg = (std::max(p->r_max, 1) + 7) / 8 * 8;
+  float* G = static_cast<float*>(ws);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  lora::RowProdLaunch r{};
+  r.hdr = p->d.hdr;
+  r.ent = p->d.mrb;
+  r.perm = p->d.m_perm;
+  r.meta = static_cast<const lora::SlotMeta*>(t->dev_meta);
+  r.n = p->n;
+  r.num_slots = t->num_slots;
+  r.d_in = t->d_in;
+  r.d_out = t->d_out;
+  r.count_word = lora::HDR_NMRB;
+  r.ent_rows = lora::MRB_ROWS;
+  r.ent_ub = ub_mrb(p);
+  r.r_max = p->r_max;
+  r.rank4 = p->rank4;
+  r.do_g = true;
+  r.dY = dY;
+  r.lddy = lddy;
+  r.Gf = G;
+  r.ldg = ldg;
+  hipError_t e = p->r_max > 0 ? lora::launch_rowprod(r, s) : hipSuccess;
+  if (e == hipSuccess) e = lora::launch_grad_x_mfma(grad_x_launch(p), G, ldg, dX, dx_dtype, lddx, s);
   if (e != hipSuccess) return hip_fail(e, "input-gradient launch");
   return ok();
 }
@@ -1270,25 +1321,36 @@ lora_status lora_backward(const lora_plan* p, const void* X, lora_dtype x_dtype,
   const size_t off = al256(lora_grad_workspace_bytes(p));
   char* wsb = static_cast<char*>(ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // the input gradient on the second stream beside the adapter gradients:
-  // both read the plan and dY as they are when the call is made, and write
-  // disjoint outputs and workspace parts
+  lora::GradLaunch g;
+  st = grad_setup(p, X, x_dtype, ldx, dY, dy_dtype, lddy, H_saved, ldh, dA, dB, accumulate, wsb, off, g);
+  if (st != LORA_OK) return st;
+  // H and G once for both gradients; then the input gradient's expand on the
+  // second stream beside the adapter gradients' reduction: both read the first
+  // stage, and write disjoint outputs
+  float* G = reinterpret_cast<float*>(wsb + off);
+  const int64_t ldg = (std::max(p->r_max, 1) + 7) / 8 * 8;
   std::unique_lock<std::mutex> lk(g_aux_mutex);
   AuxStream* aux = p->n > 0 ? aux_stream(s) : nullptr;
-  hipError_t e;
-  if (aux != nullptr && (e = hipEventRecord(aux->fork, s)) != hipSuccess) return hip_fail(e, "fork record");
-  st = lora_grad(p, X, x_dtype, ldx, dY, dy_dtype, lddy, H_saved, ldh, dA, dB, accumulate, wsb, off,
-                 stream);
-  if (st != LORA_OK) return st;
-  if (aux == nullptr) {
-    lk.unlock();
-    return lora_grad_x(p, dY, dy_dtype, lddy, dX, dx_dtype, lddx, wsb + off, ws_bytes - off, stream);
+  if (aux == nullptr) lk.unlock();
+  hipError_t e = lora::launch_grad_hg_mfma(g, p->n > 0 ? G : nullptr, ldg, s);
+  if (e != hipSuccess) return hip_fail(e, "gradient launch");
+  hipStream_t sx = s;
+  if (aux != nullptr) {
+    if ((e = hipEventRecord(aux->fork, s)) != hipSuccess) return hip_fail(e, "fork record");
+    if ((e = hipStreamWaitEvent(aux->s, aux->fork, 0)) != hipSuccess) return hip_fail(e, "fork wait");
+    sx = aux->s;
   }
-  if ((e = hipStreamWaitEvent(aux->s, aux->fork, 0)) != hipSuccess) return hip_fail(e, "fork wait");
-  st = lora_grad_x(p, dY, dy_dtype, lddy, dX, dx_dtype, lddx, wsb + off, ws_bytes - off, aux->s);
-  if ((e = hipEventRecord(aux->join, aux->s)) != hipSuccess) return hip_fail(e, "join record");
-  if ((e = hipStreamWaitEvent(s, aux->join, 0)) != hipSuccess) return hip_fail(e, "join wait");
-  return st;
+  hipError_t ex = hipSuccess;
+  if (p->n > 0) ex = lora::launch_grad_x_mfma(grad_x_launch(p), G, ldg, dX, dx_dtype, lddx, sx);
+  if (aux != nullptr && (e = hipEventRecord(aux->join, aux->s)) != hipSuccess)
+    return hip_fail(e, "join record");
+  e = lora::launch_grad_dadb_mfma(g, s);
+  hipError_t ej = hipSuccess;
+  if (aux != nullptr) ej = hipStreamWaitEvent(s, aux->join, 0);
+  if (ex != hipSuccess) return hip_fail(ex, "input-gradient launch");
+  if (e != hipSuccess) return hip_fail(e, "gradient launch");
+  if (ej != hipSuccess) return hip_fail(ej, "join wait");
+  return ok();
 }
 
 // ---- adapter-local optimizer step ---------------------------------------------

@@ -764,15 +764,13 @@ __global__ __launch_bounds__(256, (KSM == 1 || (YBF16 && KSM == 2 && U == 1)) ? 
 // LDS, each wave loading the B rows of its own columns, no barrier in the
 // column loop).
 // ---------------------------------------------------------------------------
-// WT (input gradient): the weight is B_a as stored, [K][r] with K = p.d_in,
-// gathered (eight 2-byte loads per lane and k-step, packed when multiplied).
-template <int NT, bool WT>
+template <int NT>
 __global__ __launch_bounds__(256) void shrink_fine_kernel(FwdArgs p) {
   constexpr int N = 4 * NT, CH = N < 16 ? N : 16;
   __shared__ f32x4 s_red[2 * CH * 64];
   const int lane = threadIdx.x & 63, w = wave_id();
   const int mrow = lane & 15, kg = (lane >> 4) * 8;
-  if (!p.force_fine && p.hdr[HDR_RB_ROWS] != RB_FINE) return;   // the coarse kernel's batch
+  if (p.hdr[HDR_RB_ROWS] != RB_FINE) return;   // the coarse kernel's batch
   int first, count;
   entry_range(p, first, count);
   const int nks = shrink_splits(p, count);
@@ -783,7 +781,7 @@ __global__ __launch_bounds__(256) void shrink_fine_kernel(FwdArgs p) {
     const int a = ck_slot(p.hdr, en.x, p.num_slots), p0 = en.y, rows = en.z;
     const Slot m = load_slot(p.meta, a);
     const int r = m.rank;
-    const rsrc_t A = make_rsrc(WT ? m.B : m.A, (uint32_t)r * (uint32_t)p.d_in * 2u);
+    const rsrc_t A = make_rsrc(m.A, (uint32_t)r * (uint32_t)p.d_in * 2u);
     int kb, ke;
     kslice(p.d_in, nks, ks, kb, ke);
     const int kend = max(ke, 8);
@@ -806,7 +804,7 @@ __global__ __launch_bounds__(256) void shrink_fine_kernel(FwdArgs p) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int j = nt * 16 + mrow;
-      arow[nt] = WT ? (uint32_t)(j < r ? j : r - 1) : (uint32_t)(j < r ? j : r - 1) * (uint32_t)p.d_in;
+      arow[nt] = (uint32_t)(j < r ? j : r - 1) * (uint32_t)p.d_in;
     }
     f32x4 acc[N];
 #pragma unroll
@@ -814,8 +812,7 @@ __global__ __launch_bounds__(256) void shrink_fine_kernel(FwdArgs p) {
 
     struct Buf {
       bf16x8 x[4];
-      bf16x8 a[WT ? 1 : NT];
-      uint32_t e[WT ? NT : 1][8];
+      bf16x8 a[NT];
       bool kv;
     };
     auto load = [&](Buf& b, int i) {
@@ -823,27 +820,16 @@ __global__ __launch_bounds__(256) void shrink_fine_kernel(FwdArgs p) {
       b.kv = k < ke;
       const int kk = k < kend ? k : kend - 8;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        if (!WT) {
-          b.a[WT ? 0 : nt] = as_bf16x8(bload16(A, (arow[nt] + (uint32_t)kk) * 2u));
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-            b.e[WT ? nt : 0][q] = bload_u16(A, ((uint32_t)(kk + q) * (uint32_t)r + arow[nt]) * 2u);
-        }
-      }
+      for (int nt = 0; nt < NT; ++nt) b.a[nt] = as_bf16x8(bload16(A, (arow[nt] + (uint32_t)kk) * 2u));
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) b.x[mt] = as_bf16x8(ldg16(xrow[mt] + kk));
     };
     auto compute = [&](const Buf& b) {
-      bf16x8 av[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) av[nt] = WT ? pack_bf16x8(b.e[WT ? nt : 0]) : b.a[WT ? 0 : nt];
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
         const bf16x8 xo = sel(b.kv, b.x[mt]);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma_16x16x32(xo, av[nt], acc[mt * NT + nt]);
+        for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma_16x16x32(xo, b.a[nt], acc[mt * NT + nt]);
       }
     };
     // rounds double buffered in registers; one exit, at the end of a pair
@@ -1729,10 +1715,10 @@ hipError_t launch_shrink_mfma(const OpLaunch& o, const void* X, int64_t ldx, flo
   const int nt = (o.r_max + 15) / 16;
   // the plan picks the block size on the device: both kernels are launched and
   // the one for the other size returns at once
-  hipError_t err = nt <= 1   ? launch(shrink_fine_kernel<1, false>, gridf, a, s)
-                   : nt <= 2 ? launch(shrink_fine_kernel<2, false>, gridf, a, s)
-                   : nt <= 4 ? launch(shrink_fine_kernel<4, false>, gridf, a, s)
-                             : launch(shrink_fine_kernel<8, false>, gridf, a, s);
+  hipError_t err = nt <= 1   ? launch(shrink_fine_kernel<1>, gridf, a, s)
+                   : nt <= 2 ? launch(shrink_fine_kernel<2>, gridf, a, s)
+                   : nt <= 4 ? launch(shrink_fine_kernel<4>, gridf, a, s)
+                             : launch(shrink_fine_kernel<8>, gridf, a, s);
   if (err != hipSuccess) return err;
   // one 32-wide k-step per batch: the 4096 x 256-row prefill shrink measured
   // 41 us at one step, 42 at two and 46 at four (fewer requests in flight per
@@ -1744,27 +1730,15 @@ hipError_t launch_shrink_mfma(const OpLaunch& o, const void* X, int64_t ldx, flo
 }
 
 // Input gradient over the plan's masked 64-row blocks (o.rb, o.perm and
-// o.count_word describe them; o.d_in is the width of dY, o.d_out that of dX):
-// G = dY B_a into d-sliced planes, then dX += s_a G A_a, both weights read as
-// stored through gathers.
-hipError_t launch_grad_x_mfma(const OpLaunch& o, const void* dY, int64_t lddy, float* H, int64_t ldh,
-                              int64_t hp_stride, void* dX, lora_dtype dx_dtype, int64_t lddx,
-                              hipStream_t s) {
+// o.count_word describe them; o.d_out is the width of dX): dX += s_a G A_a from
+// G's float32 rows, A_a read as stored through gathers.
+hipError_t launch_grad_x_mfma(const OpLaunch& o, const float* G, int64_t ldg, void* dX,
+                              lora_dtype dx_dtype, int64_t lddx, hipStream_t s) {
   FwdArgs a = base_args(o);
-  a.X = reinterpret_cast<const uint16_t*>(dY);
-  a.ldx = lddy;
-  a.H = H;
-  a.ldh = ldh;
-  a.ks_max = SHRINK_KS_MAX;
-  a.hp_stride = hp_stride;
+  a.H = const_cast<float*>(G);
+  a.ldh = ldg;
+  a.ks_max = 1;
   a.force_fine = 1;
-  const int nt = (o.r_max + 15) / 16;
-  const int grid1 = round8(std::min<long long>((long long)o.fine_ub * a.ks_max, 2048));
-  hipError_t err = nt <= 1   ? launch(shrink_fine_kernel<1, true>, grid1, a, s)
-                   : nt <= 2 ? launch(shrink_fine_kernel<2, true>, grid1, a, s)
-                   : nt <= 4 ? launch(shrink_fine_kernel<4, true>, grid1, a, s)
-                             : launch(shrink_fine_kernel<8, true>, grid1, a, s);
-  if (err != hipSuccess) return err;
   a.Y = dX;
   a.ldy = lddx;
   a.cw = 1024;

@@ -5,16 +5,12 @@
 //
 //   H = X_m A_a^T,  G = dY_m B_a,  dB_a = s_a dY_m^T H,  dA_a = s_a G^T X_m.
 //
-// Matrix-core path, three launches:
-//  1. per trainable row block (<= 64 rows) and d-slice: partial H and G over
-//     the slice, written transposed into fp32 "planes" [j][column], where row i
-//     of block e sits in column 64 e + i.  G's second operand is gathered from
-//     B_a as stored ([d_out][r], eight 2-byte loads per lane and k-step).
-//  2. the slice planes summed in slice order and split into bf16 hi + lo.
-//  3. per adapter and 256-wide column tile of dB or dA: a fixed-order
-//     reduction over the adapter's trainable rows, one 64-row block per step;
-//     the row tile is transposed through LDS and meets the hi / lo planes on
-//     the matrix cores.
+// Matrix-core path, two launches:
+//  1. H and G of every trainable row (rowprod.hip), written transposed as bf16
+//     hi + lo "planes" [j][column], where row i of block e (<= 64 rows of one
+//     adapter) sits in column 64 e + i.
+//  2. per adapter and column tile of dB or dA: a fixed-order reduction over the
+//     adapter's trainable rows, one 64-row block per step.
 // Rows outside T_a^m are never read.  No floating-point atomics anywhere, so
 // the result is the same bytes run to run.
 #include <algorithm>
@@ -47,7 +43,6 @@ struct GradArgs {
   float* dA[GRAD_SLOT_GROUP];             // [r_a, d_in] per slot, nullptr = skip
   float* dB[GRAD_SLOT_GROUP];             // [d_out, r_a] per slot
   float* hg;
-  int32_t ks;
   int32_t p_stride;
   int32_t r_pad;
   uint16_t* fin;            // summed planes, bf16: [which][hi, lo][j][column]
@@ -57,336 +52,104 @@ __device__ __forceinline__ uint16_t* fin_plane(const GradArgs& g, int which, int
   return g.fin + ((int64_t)(which * 2 + hl) * g.r_pad) * g.p_stride;
 }
 
-__device__ __forceinline__ float* plane(const GradArgs& g, int which, int ks) {
-  return g.hg + ((int64_t)(which * g.ks + ks) * g.r_pad) * g.p_stride;
-}
-
-// d-slices actually used: enough (row block, slice) tiles to cover the chip
-// once (about 256), at most g.ks (the workspace holds g.ks slice planes)
-__device__ __forceinline__ int active_splits(const GradArgs& g, int n_blocks) {
-  return max(1, min(g.ks, 256 / max(n_blocks, 1)));
-}
-
-// slice of a dimension for split ks, in multiples of 128
-__device__ __forceinline__ void slice(int d, int nks, int ks, int& b, int& e) {
-  const int w = ((d + nks - 1) / nks + 127) / 128 * 128;
-  b = min(d, ks * w);
-  e = min(d, b + w);
+__device__ __forceinline__ float* plane(const GradArgs& g, int which) {
+  return g.hg + (int64_t)which * g.r_pad * g.p_stride;
 }
 
 // ---------------------------------------------------------------------------
-// stage 1 (matrix cores): partial H and G for one (row block, slice).  Both are
-// shrink-shaped products (rows x d-slice times rank x d-slice), streamed with
-// double-buffered 16-byte loads.
-// ---------------------------------------------------------------------------
-// acc_h += rows(xr) W1^T over k in [k1b, k1e) and acc_g += rows(yr) W2^T over
-// k in [k2b, k2e), both with k-steps kb + w * 32 + i * 128.  Each round requests
-// one batch of U k-steps of both products (every load unconditional, from a
-// clamped address) and then feeds the matrix cores, so the second product's
-// loads overlap the first one's arithmetic and nothing waits behind a branch.
-// Every tile is computed (tiles past the rows or the rank are never stored).
-template <int MT, int NT, int U, bool DB>
-__device__ __forceinline__ void rows_times_w2(f32x4 (&acc_h)[MT * NT], f32x4 (&acc_g)[MT * NT],
-                                              const uint16_t* (&xr)[MT], rsrc_t W1,
-                                              const uint32_t (&wr1)[NT], int k1b, int k1e,
-                                              const uint16_t* (&yr)[MT], rsrc_t W2,
-                                              const uint32_t (&wr2)[NT], int k2b, int k2e,
-                                              int r2) {
-  const int kg = ((threadIdx.x & 63) >> 4) * 8 + wave_id() * 32;
-  struct Buf {
-    bf16x8 x[U][MT];
-    bf16x8 w[U][NT];
-    uint32_t e[U][NT][8];   // gathered values, packed only when multiplied
-    bool kv[U];
-  };
-  // gather = false: W is [rows][K] (K contiguous), wr[nt] the row offset;
-  // gather = true:  W is [K][r] (B_a as stored), wr[nt] the column, and the
-  //                 eight K values of a lane are eight 2-byte loads r apart
-  auto load = [&](Buf& b, const uint16_t* (&rr)[MT], rsrc_t W, const uint32_t (&wr)[NT], int kb,
-                  int ke, bool gather) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = kb + u * 128 + kg;
-      b.kv[u] = k < ke;
-      const int kk = k < ke ? k : ke - 8;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) b.x[u][mt] = as_bf16x8(ldg16(rr[mt] + kk));
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        if (!gather) {
-          b.w[u][nt] = as_bf16x8(bload16(W, (wr[nt] + (uint32_t)kk) * 2u));
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i)
-            b.e[u][nt][i] = bload_u16(W, ((uint32_t)(kk + i) * (uint32_t)r2 + wr[nt]) * 2u);
-        }
-      }
-    }
-  };
-  auto compute = [&](const Buf& b, f32x4 (&acc)[MT * NT], bool gather) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      bf16x8 wv[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) wv[nt] = gather ? pack_bf16x8(b.e[u][nt]) : b.w[u][nt];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const bf16x8 xo = sel(b.kv[u], b.x[u][mt]);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt * NT + nt] = mfma_16x16x32(xo, wv[nt], acc[mt * NT + nt]);
-      }
-    }
-  };
-  const int n1 = max(0, (k1e - k1b + U * 128 - 1) / (U * 128));
-  const int n2 = max(0, (k2e - k2b + U * 128 - 1) / (U * 128));
-  const int rounds = max(n1, n2);
-  const int e1 = max(k1e, 8), e2 = max(k2e, 8);
-  if (DB) {
-    // rounds double buffered in registers: round i + 1 is requested before
-    // round i is multiplied, so the memory stream never pauses for the
-    // arithmetic (rounds past the end read clamped addresses and add zeros);
-    // one exit, at the end of a pair of rounds
-    Buf h0, g0, h1, g1;
-    load(h0, xr, W1, wr1, k1b, e1, false);
-    load(g0, yr, W2, wr2, k2b, e2, true);
-    for (int i = 0; i < rounds; i += 2) {
-      load(h1, xr, W1, wr1, k1b + (i + 1) * U * 128, e1, false);
-      load(g1, yr, W2, wr2, k2b + (i + 1) * U * 128, e2, true);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(h0, acc_h, false);
-      compute(g0, acc_g, true);
-      load(h0, xr, W1, wr1, k1b + (i + 2) * U * 128, e1, false);
-      load(g0, yr, W2, wr2, k2b + (i + 2) * U * 128, e2, true);
-      __builtin_amdgcn_sched_barrier(0);
-      compute(h1, acc_h, false);
-      compute(g1, acc_g, true);
-      // wait states on the back edge between the last product and the loop
-      // head, where the compiler may read an accumulator register
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_nop 7");
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    for (int i = 0; i < rounds; ++i) {
-      Buf bh, bg;
-      load(bh, xr, W1, wr1, k1b + i * U * 128, e1, false);
-      load(bg, yr, W2, wr2, k2b + i * U * 128, e2, true);
-      // keep the whole round's loads ahead of its arithmetic (the scheduler
-      // would otherwise interleave them to save registers, and wait on each)
-      __builtin_amdgcn_sched_barrier(0);
-      compute(bh, acc_h, false);
-      compute(bg, acc_g, true);
-    }
-  }
-  mfma_fence();
-}
-
-// Sum the four waves' accumulators in the fixed order ((w0 + w2) + (w1 + w3)),
-// leaving the total in wave 0: waves 1-3 park CH accumulators at a time in
-// s_red (3 x CH x 64 f32x4), one barrier per chunk.  The first barrier also
-// orders this tile's writes after the previous tile's reads of s_red.
-template <int N, int CH>
-__device__ __forceinline__ void reduce_waves3(f32x4 (&acc)[N], f32x4* s_red) {
-  const int lane = threadIdx.x & 63, w = wave_id();
-#pragma unroll
-  for (int c0 = 0; c0 < N; c0 += CH) {
-    __syncthreads();
-    if (w > 0) {
-#pragma unroll
-      for (int i = 0; i < CH; ++i)
-        if (c0 + i < N) s_red[((w - 1) * CH + i) * 64 + lane] = acc[c0 + i];
-    }
-    __syncthreads();
-    if (w == 0) {
-#pragma unroll
-      for (int i = 0; i < CH; ++i)
-        if (c0 + i < N) {
-          const f32x4 a1 = s_red[(0 * CH + i) * 64 + lane];
-          const f32x4 a2 = s_red[(1 * CH + i) * 64 + lane];
-          const f32x4 a3 = s_red[(2 * CH + i) * 64 + lane];
-          acc[c0 + i] = (acc[c0 + i] + a2) + (a1 + a3);
-        }
-    }
-  }
-}
-
-#ifndef HG_U
-#define HG_U 1
-#endif
-template <int NT>
-__global__ __launch_bounds__(256) void hg_kernel(GradArgs g) {
-  constexpr int MT = MRB_ROWS / 16;                      // row tiles per block
-  constexpr int U = HG_U > 0 ? HG_U : 1;                 // k-steps per wave and round
-  constexpr bool DB = NT <= 4;                           // double-buffered rounds
-  constexpr int N = 2 * MT * NT, CH = N < 16 ? N : 16;
-  constexpr int OS = MRB_ROWS + 1;                       // LDS row stride of the plane tile
-  constexpr int RED = 3 * CH * 64, PL = NT * 16 * OS, OUT = (2 * PL + 3) / 4;
-  __shared__ f32x4 s_red[RED > OUT ? RED : OUT];
-  const int lane = threadIdx.x & 63, w = wave_id();
-  const int n_blocks = g.hdr[HDR_NMRB];
-  const int nks = active_splits(g, n_blocks);
-  const XcdRange xr = xcd_range(n_blocks * nks);
-  const uint16_t* X = reinterpret_cast<const uint16_t*>(g.X);
-  const uint16_t* dY = reinterpret_cast<const uint16_t*>(g.dY);
-  for (int tile = xr.first; tile < xr.end; tile += xr.step) {
-    const int e = tile / nks, ks = tile - e * nks;
-    const int4 en = load_entry(g.mrb, e);
-    const int a = ck_slot(g.hdr, en.x, g.num_slots), p0 = en.y, rows = en.z;
-    const Slot m = load_slot(g.meta, a);
-    const int r = m.rank;
-    const rsrc_t Aw = make_rsrc(m.A, (uint32_t)r * (uint32_t)g.d_in * 2u);
-    const rsrc_t Bw = make_rsrc(m.B, (uint32_t)g.d_out * (uint32_t)r * 2u);
-    const uint16_t* xrow[MT];
-    const uint16_t* yrow[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int i = mt * 16 + (lane & 15);
-      const int t = ck_row(g.hdr, g.m_perm[p0 + (i < rows ? i : rows - 1)], g.n_rows);
-      xrow[mt] = X + (int64_t)t * g.ldx;
-      yrow[mt] = dY + (int64_t)t * g.lddy;
-    }
-    uint32_t arow[NT], brow[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int j = nt * 16 + (lane & 15);
-      arow[nt] = (uint32_t)(j < r ? j : r - 1) * (uint32_t)g.d_in;
-      brow[nt] = (uint32_t)(j < r ? j : r - 1);
-    }
-    // acc[0 .. MT NT) : H tiles (mt, nt); acc[MT NT .. 2 MT NT) : G tiles
-    f32x4 acc[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 (&acc_h)[MT * NT] = *reinterpret_cast<f32x4(*)[MT * NT]>(&acc[0]);
-    f32x4 (&acc_g)[MT * NT] = *reinterpret_cast<f32x4(*)[MT * NT]>(&acc[MT * NT]);
-    {
-      int kb, ke, ob, oe;
-      slice(g.d_in, nks, ks, kb, ke);
-      slice(g.d_out, nks, ks, ob, oe);
-      if (g.H_saved != nullptr) ke = kb;          // H comes from the caller
-      rows_times_w2<MT, NT, U, DB>(acc_h, acc_g, xrow, Aw, arow, kb, ke, yrow, Bw, brow, ob, oe, r);
-    }
-    vmem_drained();
-    reduce_waves3<N, CH>(acc, s_red);
-    // wave 0 holds the totals; both planes' tiles [j][64 columns] are staged
-    // in LDS together and leave as whole 256-byte row pieces (one barrier, so
-    // no wave waits for the first plane's stores)
-    float* s_o = reinterpret_cast<float*>(s_red);
-    const int col0 = e * MRB_ROWS;
-    if (w == 0) {
-#pragma unroll
-      for (int which = 0; which < 2; ++which)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int i = mt * 16 + (lane >> 4) * 4 + v, j = nt * 16 + (lane & 15);
-              s_o[which * PL + j * OS + i] = i < rows ? acc[which * MT * NT + mt * NT + nt][v] : 0.0f;
-            }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-      if (which == 1 || g.H_saved == nullptr) {
-        float* pl = plane(g, which, ks);
-        for (int q = threadIdx.x; q < g.r_pad * (MRB_ROWS / 4); q += 256) {
-          const int j = q / (MRB_ROWS / 4), c4 = (q - j * (MRB_ROWS / 4)) * 4;
-          const float* so = s_o + which * PL + j * OS + c4;
-          stg_f4(pl + (int64_t)j * g.p_stride + col0 + c4, make_float4(so[0], so[1], so[2], so[3]));
-        }
-      }
-    }
-    if (g.H_saved != nullptr && w == 0) {
-      float* ph = plane(g, 0, ks);
-      for (int q = lane; q < MRB_ROWS * g.r_pad; q += 64) {
-        const int i = q / g.r_pad, j = q - i * g.r_pad;
-        float h = 0.0f;
-        if (ks == 0 && i < rows && j < r) h = g.H_saved[(int64_t)ck_row(g.hdr, g.m_perm[p0 + i], g.n_rows) * g.ldh + j];
-        ph[(int64_t)j * g.p_stride + col0 + i] = h;
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// stage 2: planes summed in slice order, split into bf16 hi / lo (8 columns per
-// thread)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void hgsum_kernel(GradArgs g) {
-  const int n_blocks = g.hdr[HDR_NMRB];
-  const int nks = active_splits(g, n_blocks);
-  const int n8 = n_blocks * (MRB_ROWS / 8);           // 8-column groups per plane row
-  const int64_t per = (int64_t)g.r_pad * n8;
-  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < 2 * per;
-       q += (int64_t)gridDim.x * 256) {
-    const int which = (int)(q / per);
-    const int64_t u = q - which * per;
-    const int j = (int)(u / n8), c = (int)(u - (int64_t)j * n8) * 8;
-    // every slice requested at once (slices past nks read the last one again
-    // and are not added), then summed in slice order
-    float4 x0[GRAD_SPLITS_MAX], x1[GRAD_SPLITS_MAX];
-#pragma unroll
-    for (int ks = 0; ks < GRAD_SPLITS_MAX; ++ks) {
-      const float* p = plane(g, which, min(ks, nks - 1)) + (int64_t)j * g.p_stride + c;
-      x0[ks] = ldg_f4(p);
-      x1[ks] = ldg_f4(p + 4);
-    }
-    float h[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < GRAD_SPLITS_MAX; ++ks) {
-      if (ks >= nks) break;
-      h[0] += x0[ks].x; h[1] += x0[ks].y; h[2] += x0[ks].z; h[3] += x0[ks].w;
-      h[4] += x1[ks].x; h[5] += x1[ks].y; h[6] += x1[ks].z; h[7] += x1[ks].w;
-    }
-    bf16x8 hi, lo;
-    split_hi_lo(h, hi, lo);
-    stg16(fin_plane(g, which, 0) + (int64_t)j * g.p_stride + c, __builtin_bit_cast(uint4, hi));
-    stg16(fin_plane(g, which, 1) + (int64_t)j * g.p_stride + c, __builtin_bit_cast(uint4, lo));
-  }
-}
-
-// ---------------------------------------------------------------------------
-// stage 3 (matrix cores): one workgroup per (slot, dB or dA, 256-column tile).
-// A step is one 64-row gradient block of the slot: every thread loads eight
-// rows x 8 columns of dY (for dB) or X (for dA), transposes them in registers
-// and writes 8 columns x 8 rows into LDS as 16-byte units, next to the step's
-// hi / lo plane columns; the next step's loads are in flight meanwhile and LDS
-// is double buffered with one barrier per step.
+// stage 2 (matrix cores): one workgroup per (slot, dB or dA, column tile).
+// A step is one 64-row gradient block of the slot: its rows of dY (for dB) or
+// X (for dA) and the block's hi / lo plane columns go straight from memory into
+// LDS (no registers), two steps ahead of the one being multiplied, with one
+// barrier per step.  The contraction runs over the rows, so the row tile is
+// read transposed, by ds_read_b64_tr_b16: 16 lanes read 4 rows x 16 columns and
+// each receives 4 rows of one column.
 //   dB[o][j] = s sum_t dY[t][o] H[t][j]:  A operand = dY^T tile, B = H plane
 //   dA[j][k] = s sum_t G[t][j] X[t][k]:   A operand = G plane, B = X^T tile
+//
+// Bound by the bytes in flight per CU: a step's rows come from HBM or the
+// last-level cache with about 2 us of latency, and a slot's steps are a serial
+// chain.  Up to rank 32 the tile is 128 columns wide and two workgroups share a
+// CU (80 KB of LDS each).  Transposing through registers with two steps in
+// flight and one workgroup per CU took 21.4 us for 2446 rows of 8 slots (4096 ->
+// 4096, rank 32) and 44 us beside the input gradient for 4705 rows of 6 slots
+// (5120, rank 16); this one 13.8 and 36.
 // ---------------------------------------------------------------------------
-// tile columns: 256, or 128 for ranks above 64 (register budget)
-constexpr int dt_ct(int NT) { return NT <= 4 ? 256 : 128; }
-constexpr int DT_ROWS = MRB_ROWS;     // rows per step: one trainable row block
-constexpr int DT_WIN = 1024;          // row ids staged per window
+template <int NT>
+struct Dt {
+  static constexpr int CT = NT == 4 ? 256 : 128;          // tile columns
+  static constexpr int ROWS = MRB_ROWS;                   // rows per step: one trainable row block
+  static constexpr int RB = CT * 2;                       // bytes per staged row
+  static constexpr int RPI = 1024 / RB;                   // rows per direct load (1 KB per wave)
+  static constexpr int RI = ROWS / RPI / 4;               // ... loads per wave and step
+  static constexpr int PL = 2 * NT * 16 * ROWS * 2;       // bytes of the hi and lo plane columns
+  static constexpr int STAGE = ROWS * RB + PL;
+  static constexpr int NS = 3;                            // steps in LDS
+  static constexpr int LPS = RI + NT;                     // direct loads per wave and step
+  static constexpr int WIN = 2048;                        // row ids staged per window
+  static constexpr int I4 = CT / 64;                      // 16-column tiles per wave
+  static_assert(NS * STAGE + WIN * 4 <= (NT <= 2 ? 80 : 160) * 1024, "LDS");
+};
 
-// LDS slot of 16-byte unit g (rows 8 g .. 8 g + 7 of a step) of column `col`
-// (a tile column, or a plane row j).  Two columns share each 256-byte line
-// and the units are permuted inside it, so that the 16 lanes of a transposing
-// write (columns 8 apart) and of a matrix-core read (16 consecutive columns)
-// both fall in 16 distinct 16-byte bank groups.
-__device__ __forceinline__ int dt_unit(int col, int g) {
-  const int r = col >> 1;
-  const int f = (r & 7) ^ ((r >> 3) & 3) ^ (((r >> 5) & 1) << 3);
-  return r * 16 + ((((col & 1) << 3) | g) ^ f);
+// What the rows past a slot's last one read (BIG).
+__device__ __align__(256) uint4 g_zero_row[32];
+
+// Direct loads through a 32-bit buffer offset (past the resource: zeros), or, for
+// matrices of 2 GiB and more (BIG), from a 64-bit address; after one of the
+// latter the compiler waits for all of them before it reads LDS.
+// (not templates: the host pass cannot resolve these builtins inside one)
+__device__ __forceinline__ void dt_dma16(rsrc_t src, uint8_t* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16, off,
+                                           0, 0, 0);
 }
+__device__ __forceinline__ void dt_dma16_far(const void* src, uint8_t* lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+// Transposing reads of two 16-column tiles (LDS byte addresses a0, a1), rows
+// +0 and +4 each (byte offsets O0, O1).  In asm, with its wait in the same
+// block: before the builtin the compiler waits for every direct load in flight.
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+template <int O0, int O1>
+__device__ __forceinline__ void dt_tr2(uint32_t a0, uint32_t a1, u32x4& v0, u32x4& v1) {
+#ifdef __HIP_DEVICE_COMPILE__
+  u32x2 p, q, r, t;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4 offset:%6\n\t"
+      "ds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
+      "ds_read_b64_tr_b16 %2, %5 offset:%6\n\t"
+      "ds_read_b64_tr_b16 %3, %5 offset:%7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(p), "=&v"(q), "=&v"(r), "=&v"(t)
+      : "v"(a0), "v"(a1), "n"(O0), "n"(O1)
+      : "memory");
+  v0 = __builtin_shufflevector(p, q, 0, 1, 2, 3);
+  v1 = __builtin_shufflevector(r, t, 0, 1, 2, 3);
+#endif
+}
+__device__ __forceinline__ uint32_t lds_addr(const uint8_t* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p;
+}
+// Wait until at most N of this wave's vector memory operations are outstanding
+// and its LDS reads are done, then meet the other waves.
+template <int N>
+__device__ __forceinline__ void dt_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// LDS layout of a step.  Row R: CT / 16 units of 32 bytes, unit u at u ^ f(R),
+// f(R) = (R & 3) | ((R >> 3 & 1) << 2), so that the 8 rows that half a wave's
+// transposing read touches lie in 8 distinct 32-byte bank groups.  Plane row
+// j (hi rows, then lo rows): 8 chunks of 16 bytes, chunk c at c ^ (j & 7).
 
 // One (slot, column tile) of dB (IS_B) or dA: the whole reduction over the
 // slot's trainable rows, then the scaled store.
-template <int NT, bool IS_B>
-__device__ __forceinline__ void dadb_tile(const GradArgs& g, int sl, int c0, uint16_t (*s_t)[dt_ct(NT) * DT_ROWS],
-                                          uint16_t (*s_p)[2 * NT * 16 * DT_ROWS], int* s_rows) {
-  constexpr int CT = dt_ct(NT);
-  constexpr int PSEG = 2 * NT * 16 * (DT_ROWS / 8);   // 16-byte plane units per step
-  constexpr int PPT = PSEG / 256;                     // per thread
-  constexpr int CSN = CT / 8, I4 = CT / 64;     // loader column segments; 16-column tiles per wave
-  static_assert(PSEG % 256 == 0, "plane units per thread");
+template <int NT, bool BIG, bool IS_B>
+__device__ __forceinline__ void dadb_tile(const GradArgs& g, int sl, int c0, uint8_t* s_ring,
+                                          int* s_rows) {
+  using D = Dt<NT>;
+  constexpr int I4 = D::I4;
   const int lane = threadIdx.x & 63, w = wave_id(), tid = threadIdx.x;
-  // loader: columns 8 cs .., rows 8 tq ..; with 128-column tiles the upper
-  // half of the threads repeats the lower half (same values, same addresses)
-  const int cs = tid % CSN, tq = (tid / CSN) & 7;
   const int a = g.slot_base + sl;
   const Slot m = load_slot(g.meta, a);
   const int r = m.rank;
@@ -398,9 +161,9 @@ __device__ __forceinline__ void dadb_tile(const GradArgs& g, int sl, int c0, uin
   const uint16_t* src = reinterpret_cast<const uint16_t*>(IS_B ? g.dY : g.X);
   const int64_t ld = IS_B ? g.lddy : g.ldx;
   const uint16_t* fin0 = fin_plane(g, IS_B ? 0 : 1, 0);
-  const uint16_t* fin1 = fin_plane(g, IS_B ? 0 : 1, 1);
-  const int lcol = c0 + cs * 8 < dcol ? c0 + cs * 8 : dcol - 8;   // clamped loader column
-  const bool lcol_ok = c0 + cs * 8 < dcol;
+  // (the lo plane follows the hi plane)
+  const rsrc_t rows_rsrc = make_rsrc(src, BIG ? 0u : (uint32_t)(((int64_t)(g.n_rows - 1) * ld + dcol) * 2));
+  const rsrc_t fin_rsrc = make_rsrc(fin0, BIG ? 0u : (uint32_t)((int64_t)2 * g.r_pad * g.p_stride * 2));
 
   f32x4 acc[I4][NT];
 #pragma unroll
@@ -408,80 +171,80 @@ __device__ __forceinline__ void dadb_tile(const GradArgs& g, int sl, int c0, uin
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int nch = (mc + DT_ROWS - 1) / DT_ROWS;
-  for (int w0 = 0; w0 < nch; w0 += DT_WIN / DT_ROWS) {
-    const int wch = min(DT_WIN / DT_ROWS, nch - w0);
+  // loader: row lr of each load, and its column per load (the swizzle depends
+  // on the row's low bits: rows of load i are RPI i past those of load 0)
+  constexpr int LPR = 64 / D::RPI;             // lanes per row
+  const int lr = lane / LPR, pc = lane % LPR;
+  // reader: fixed lane offsets
+  const int n = lane & 15, gq = lane >> 4;
+  const int f = (n >> 2) | ((gq & 1) << 2);
+  uint32_t toff[I4];
+#pragma unroll
+  for (int i4 = 0; i4 < I4; ++i4)
+    toff[i4] = (gq * 8 + (n >> 2)) * D::RB + (((w * I4 + i4) ^ f) << 5) + (n & 3) * 8;
+
+  const int nch = (mc + D::ROWS - 1) / D::ROWS;
+  for (int w0 = 0; w0 < nch; w0 += D::WIN / D::ROWS) {
+    const int wch = min(D::WIN / D::ROWS, nch - w0);
+    const int wrows = min(D::WIN, mc - w0 * D::ROWS);
     __syncthreads();
-    for (int i = tid; i < DT_WIN; i += 256) {
-      const int p = w0 * DT_ROWS + i;
-      s_rows[i] = ck_row(g.hdr, g.m_perm[moff + (p < mc ? p : mc - 1)], g.n_rows);
-    }
+    for (int i = tid; i < wch * D::ROWS; i += 256)
+      s_rows[i] = i < wrows ? ck_row(g.hdr, g.m_perm[moff + w0 * D::ROWS + i], g.n_rows) : -1;
     __syncthreads();
 
-    struct Step {
-      uint4 t[8];
-      uint4 p[PPT];
-    };
-    // raw loads of step cc (clamped to the window's last step; steps past it
-    // are staged as zero rows).  Step cc is row block blk0 + w0 + cc, so its
-    // plane columns are that block's 64 columns.
-    auto load = [&](Step& q, int cc) {
+    // the direct loads of step cc into its ring slot (past the window's last
+    // step: that step again, into a slot nobody reads)
+    auto issue = [&](int cc) {
+      uint8_t* dst = s_ring + (cc % D::NS) * D::STAGE;
       cc = min(cc, wch - 1);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        q.t[i] = ldg16(src + (int64_t)s_rows[cc * DT_ROWS + tq * 8 + i] * ld + lcol);
-      const int col0 = (blk0 + w0 + cc) * DT_ROWS;
+      for (int i = 0; i < D::RI; ++i) {
+        const int R = (D::RI * w + i) * D::RPI + lr;
+        const int t = s_rows[cc * D::ROWS + R];
+        int col = c0 + ((pc ^ (((R & 3) | ((R >> 3 & 1) << 2)) << 1)) << 3);
+        col = col < dcol ? col : dcol - 8;      // clamped; such columns are not stored
+        if constexpr (BIG) {
+          const uint64_t real = reinterpret_cast<uint64_t>(src + (int64_t)max(t, 0) * ld + col);
+          const uint64_t zero = reinterpret_cast<uint64_t>(&g_zero_row[0]);
+          dt_dma16_far(reinterpret_cast<const void*>(t >= 0 ? real : zero), dst + (D::RI * w + i) * 1024);
+        } else {
+          const uint32_t off = ((uint32_t)t * (uint32_t)ld + (uint32_t)col) * 2u;
+          dt_dma16(rows_rsrc, dst + (D::RI * w + i) * 1024, t >= 0 ? off : 0x80000000u);
+        }
+      }
+      const int col0 = (blk0 + w0 + cc) * D::ROWS;
 #pragma unroll
-      for (int h = 0; h < PPT; ++h) {
-        const int u = tid + 256 * h, jr = u >> 3, gg = u & 7;
-        const int hl = jr / (NT * 16), j = jr - hl * (NT * 16);
-        q.p[h] = ldg16((hl ? fin1 : fin0) + (int64_t)j * g.p_stride + col0 + gg * 8);
+      for (int i = 0; i < NT; ++i) {
+        const int q = (NT * w + i) * 64 + lane, jr = q >> 3;
+        const int hl = jr / (NT * 16), j = min(jr - hl * (NT * 16), g.r_pad - 1);
+        const int c8 = col0 + (((q & 7) ^ (jr & 7)) << 3);
+        uint8_t* d = dst + D::ROWS * D::RB + (NT * w + i) * 1024;
+        if constexpr (BIG) dt_dma16_far(fin0 + ((int64_t)(hl * g.r_pad + j)) * g.p_stride + c8, d);
+        else dt_dma16(fin_rsrc, d, ((uint32_t)(hl * g.r_pad + j) * (uint32_t)g.p_stride + (uint32_t)c8) * 2u);
       }
     };
-    auto stage = [&](const Step& q, int cc, int buf) {
-      const int rows_left = mc - (w0 + cc) * DT_ROWS;
-      uint32_t v[8][4];
+    auto mma = [&](int cc) {
+      const uint8_t* rows = s_ring + (cc % D::NS) * D::STAGE;
+      const uint8_t* pl = rows + D::ROWS * D::RB;
+      const uint32_t base = lds_addr(rows);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bool ok = lcol_ok && tq * 8 + i < rows_left;
-        v[i][0] = ok ? q.t[i].x : 0u;
-        v[i][1] = ok ? q.t[i].y : 0u;
-        v[i][2] = ok ? q.t[i].z : 0u;
-        v[i][3] = ok ? q.t[i].w : 0u;
-      }
-      // 8 rows x 8 columns -> 8 columns x 8 rows (bf16 pairs through byte permutes)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
-        uint4 o;
-        o.x = __builtin_amdgcn_perm(v[1][c >> 1], v[0][c >> 1], sel);
-        o.y = __builtin_amdgcn_perm(v[3][c >> 1], v[2][c >> 1], sel);
-        o.z = __builtin_amdgcn_perm(v[5][c >> 1], v[4][c >> 1], sel);
-        o.w = __builtin_amdgcn_perm(v[7][c >> 1], v[6][c >> 1], sel);
-        *reinterpret_cast<uint4*>(&s_t[buf][dt_unit(cs * 8 + c, tq) * 8]) = o;
-      }
-#pragma unroll
-      for (int h = 0; h < PPT; ++h) {
-        const int u = tid + 256 * h;
-        *reinterpret_cast<uint4*>(&s_p[buf][dt_unit(u >> 3, u & 7) * 8]) = q.p[h];
-      }
-    };
-    auto mma = [&](int buf) {
-      const int gq = lane >> 4, n = lane & 15;
-#pragma unroll
-      for (int kc = 0; kc < DT_ROWS / 32; ++kc) {
-        const int gu = kc * 4 + gq;
+      for (int kc = 0; kc < D::ROWS / 32; ++kc) {
         bf16x8 hi[NT], lo[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-          hi[nt] = as_bf16x8(*reinterpret_cast<const uint4*>(&s_p[buf][dt_unit(nt * 16 + n, gu) * 8]));
-          lo[nt] = as_bf16x8(
-              *reinterpret_cast<const uint4*>(&s_p[buf][dt_unit((NT + nt) * 16 + n, gu) * 8]));
+          const int ch = ((kc * 4 + gq) ^ (n & 7)) << 4;
+          hi[nt] = *reinterpret_cast<const bf16x8*>(pl + (nt * 16 + n) * 128 + ch);
+          lo[nt] = *reinterpret_cast<const bf16x8*>(pl + ((NT + nt) * 16 + n) * 128 + ch);
+        }
+        u32x4 tr[I4];
+#pragma unroll
+        for (int i4 = 0; i4 < I4; i4 += 2) {
+          if (kc == 0) dt_tr2<0, 4 * D::RB>(base + toff[i4], base + toff[i4 + 1], tr[i4], tr[i4 + 1]);
+          else dt_tr2<32 * D::RB, 36 * D::RB>(base + toff[i4], base + toff[i4 + 1], tr[i4], tr[i4 + 1]);
         }
 #pragma unroll
         for (int i4 = 0; i4 < I4; ++i4) {
-          const int col = w * (16 * I4) + i4 * 16 + n;
-          const bf16x8 tv = as_bf16x8(*reinterpret_cast<const uint4*>(&s_t[buf][dt_unit(col, gu) * 8]));
+          const bf16x8 tv = __builtin_bit_cast(bf16x8, tr[i4]);
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt) {
             if (IS_B) {
@@ -495,26 +258,17 @@ __device__ __forceinline__ void dadb_tile(const GradArgs& g, int sl, int c0, uin
         }
       }
     };
-    // Steps double buffered in registers (the next step's loads are in flight
-    // while a step is staged and multiplied); one exit, at the end of a pair
-    // of steps, and no memory operation behind a branch, so the compiler's
-    // wait counts stay exact.  LDS buffer cc & 1: a step is staged only after
-    // the barrier of the step before, which every wave passes after its
-    // products of the step before that.
-    Step b0, b1;
-    load(b0, 0);
-    for (int cc = 0; cc < wch; cc += 2) {
-      load(b1, cc + 1);
-      __builtin_amdgcn_sched_barrier(0);       // requests stay ahead of the staging
-      stage(b0, cc, 0);
-      __syncthreads();
-      mma(0);
-      load(b0, cc + 2);
-      __builtin_amdgcn_sched_barrier(0);
-      stage(b1, cc + 1, 1);
-      __syncthreads();
-      mma(1);
+    // Step cc's loads are waited for while step cc + 1's stay in flight; after
+    // the barrier every wave has finished step cc - 1, whose slot takes step
+    // cc + 2.
+    issue(0);
+    issue(1);
+    for (int cc = 0; cc < wch; ++cc) {
+      dt_barrier<D::LPS>();
+      issue(cc + 2);
+      mma(cc);
     }
+    dt_barrier<0>();       // the loads past the last step have landed
   }
 
   mfma_fence();
@@ -543,12 +297,14 @@ __device__ __forceinline__ void dadb_tile(const GradArgs& g, int sl, int c0, uin
     }
 }
 
-template <int NT>
+template <int NT, bool BIG>
 __global__ __launch_bounds__(256) void dadb_kernel(GradArgs g) {
-  constexpr int CT = dt_ct(NT);
-  __shared__ __align__(16) uint16_t s_t[2][CT * DT_ROWS];
-  __shared__ __align__(16) uint16_t s_p[2][2 * NT * 16 * DT_ROWS];   // [hl][j] columns
-  __shared__ int s_rows[DT_WIN];
+  using D = Dt<NT>;
+  constexpr int CT = D::CT;
+  // (one LDS object: with two, the compiler waits for every direct load before
+  // each LDS read)
+  __shared__ __align__(1024) uint8_t s_ring[D::NS * D::STAGE + D::WIN * 4];
+  int* const s_rows = reinterpret_cast<int*>(s_ring + D::NS * D::STAGE);
   const int nbB = (g.d_out + CT - 1) / CT, nbA = (g.d_in + CT - 1) / CT, nbt = nbB + nbA;
   // tiles dealt round-robin over the XCDs: a slot with many rows is then read by
   // all eight of them (one slot per XCD left one XCD streaming the largest
@@ -558,15 +314,15 @@ __global__ __launch_bounds__(256) void dadb_kernel(GradArgs g) {
     const int r = uni(g.meta[g.slot_base + sl].rank);
     if (r <= 0) continue;
     if (c < nbB) {
-      if (g.dB[sl] != nullptr) dadb_tile<NT, true>(g, sl, c * CT, s_t, s_p, s_rows);
+      if (g.dB[sl] != nullptr) dadb_tile<NT, BIG, true>(g, sl, c * CT, s_ring, s_rows);
     } else {
-      if (g.dA[sl] != nullptr) dadb_tile<NT, false>(g, sl, (c - nbB) * CT, s_t, s_p, s_rows);
+      if (g.dA[sl] != nullptr) dadb_tile<NT, BIG, false>(g, sl, (c - nbB) * CT, s_ring, s_rows);
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// vector-ALU path (any f32 / bf16 storage): same planes with one slice
+// vector-ALU path (any f32 / bf16 storage): the same planes in float32
 // ---------------------------------------------------------------------------
 template <bool BF16>
 __device__ __forceinline__ float ldv(const void* p, int64_t i) {
@@ -582,8 +338,8 @@ __global__ __launch_bounds__(256) void hg_valu_kernel(GradArgs g) {
     const int a = ck_slot(g.hdr, en.x, g.num_slots), p0 = en.y, rows = en.z;
     const Slot m = load_slot(g.meta, a);
     const int r = m.rank;
-    float* ph = plane(g, 0, 0);
-    float* pg = plane(g, 1, 0);
+    float* ph = plane(g, 0);
+    float* pg = plane(g, 1);
     for (int q = threadIdx.x; q < MRB_ROWS * g.r_pad; q += blockDim.x) {
       const int i = q / g.r_pad, j = q - i * g.r_pad;
       float h = 0.0f, gg = 0.0f;
@@ -633,7 +389,7 @@ __global__ __launch_bounds__(256) void dadb_valu_kernel(GradArgs g) {
     const int moff = g.m_offsets[a], blk0 = g.m_blk[a];
     const int mc = ck_count(g.hdr, moff, g.m_counts[a], g.n_rows);
     if (mc == 0 && g.accumulate) continue;
-    const float* pl = plane(g, isB ? 0 : 1, 0) + (int64_t)j * g.p_stride;
+    const float* pl = plane(g, isB ? 0 : 1) + (int64_t)j * g.p_stride;
     float acc = 0.0f;
     for (int p = 0; p < mc; ++p) {
       const int t = ck_row(g.hdr, g.m_perm[moff + p], g.n_rows);
@@ -668,7 +424,6 @@ GradArgs make_args(const GradLaunch& l) {
   g.ldh = l.ldh;
   g.accumulate = l.accumulate;
   g.hg = l.hg;
-  g.ks = l.k_splits;
   g.p_stride = l.p_stride;
   g.r_pad = l.r_pad;
   g.fin = l.fin;
@@ -694,21 +449,20 @@ bool set_group(const GradLaunch& l, GradArgs& g, int base) {
 template <int NT>
 hipError_t launch_nt(const GradLaunch& l, const GradArgs& g, hipStream_t s) {
   hipError_t err;
-  const int grid1 = round8(std::min<long long>((long long)l.o.rb_ub * l.k_splits, 4096));
-  hipLaunchKernelGGL((hg_kernel<NT>), dim3(grid1), dim3(256), 0, s, g);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  const long long groups = 2LL * l.r_pad * l.o.rb_ub * (MRB_ROWS / 8);   // 8-column groups (upper bound)
-  const int grid2 = (int)std::max<long long>(1, std::min<long long>((groups + 255) / 256, 4096));
-  hipLaunchKernelGGL(hgsum_kernel, dim3(grid2), dim3(256), 0, s, g);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
+  // row matrices and planes that 32-bit buffer offsets reach (one bit marks
+  // offsets past the end)
+  const int64_t reach = (int64_t)1 << 31;
+  const bool big = ((int64_t)l.o.n * std::max(l.ldx, l.lddy)) * 2 >= reach ||
+                   (int64_t)2 * l.r_pad * l.p_stride * 2 >= reach;
   for (int base = 0; base < l.o.num_slots; base += GRAD_SLOT_GROUP) {
     GradArgs gg = g;
     if (!set_group(l, gg, base)) continue;
-    constexpr int CT = dt_ct(NT);
+    constexpr int CT = Dt<NT>::CT;
     const long long tiles = (long long)gg.slot_count *
                             ((l.o.d_out + CT - 1) / CT + (l.o.d_in + CT - 1) / CT);
     const int grid3 = round8(std::min<long long>(tiles, 8192));
-    hipLaunchKernelGGL((dadb_kernel<NT>), dim3(grid3), dim3(256), 0, s, gg);
+    if (big) hipLaunchKernelGGL((dadb_kernel<NT, true>), dim3(grid3), dim3(256), 0, s, gg);
+    else hipLaunchKernelGGL((dadb_kernel<NT, false>), dim3(grid3), dim3(256), 0, s, gg);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   return hipSuccess;
@@ -716,7 +470,37 @@ hipError_t launch_nt(const GradLaunch& l, const GradArgs& g, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_grad_mfma(const GradLaunch& l, hipStream_t s) {
+hipError_t launch_grad_hg_mfma(const GradLaunch& l, float* Gf, int64_t ldg, hipStream_t s) {
+  RowProdLaunch r{};
+  r.hdr = l.o.hdr;
+  r.ent = l.o.rb;
+  r.perm = l.m_perm;
+  r.meta = l.o.meta;
+  r.n = l.o.n;
+  r.num_slots = l.o.num_slots;
+  r.d_in = l.o.d_in;
+  r.d_out = l.o.d_out;
+  r.count_word = l.o.count_word;
+  r.ent_rows = MRB_ROWS;
+  r.ent_ub = l.o.rb_ub;
+  r.r_max = l.o.r_max;
+  r.rank4 = l.rank4;
+  r.do_h = r.do_g = true;
+  r.X = l.X;
+  r.ldx = l.ldx;
+  r.dY = l.dY;
+  r.lddy = l.lddy;
+  r.H_saved = l.H_saved;
+  r.ld_saved = l.ldh;
+  r.Gf = Gf;
+  r.ldg = ldg;
+  r.fin = l.fin;
+  r.p_stride = l.p_stride;
+  r.r_pad = l.r_pad;
+  return launch_rowprod(r, s);
+}
+
+hipError_t launch_grad_dadb_mfma(const GradLaunch& l, hipStream_t s) {
   const GradArgs g = make_args(l);
   const int nt = (l.o.r_max + 15) / 16;
   if (nt <= 1) return launch_nt<1>(l, g, s);

@@ -155,11 +155,38 @@ hipError_t launch_shrink_mfma(const OpLaunch& o, const void* X, int64_t ldx, flo
 hipError_t launch_expand_mfma(const OpLaunch& o, const float* H, int64_t ldh, int32_t ks_max,
                               int64_t hp_stride, void* Y, lora_dtype y_dtype, int64_t ldy,
                               hipStream_t s);
-// input gradient dX += s G A_a with G = dY B_a, over the entries o describes
-// (the plan's masked blocks); H holds SHRINK_KS_MAX partial planes
-hipError_t launch_grad_x_mfma(const OpLaunch& o, const void* dY, int64_t lddy, float* H, int64_t ldh,
-                              int64_t hp_stride, void* dX, lora_dtype dx_dtype, int64_t lddx,
-                              hipStream_t s);
+// H[t] = X[t] A_a^T and / or G[t] = dY[t] B_a for the rows of the entries (bf16
+// rows and weights, matrix cores), each over the whole of d_in / d_out
+struct RowProdLaunch {
+  const int32_t* hdr;
+  const int4* ent;              // row-block entries {adapter, first index into perm, rows, 0}
+  const int32_t* perm;
+  const SlotMeta* meta;
+  int32_t n, num_slots, d_in, d_out;
+  int32_t count_word;           // header word holding the entry count
+  int32_t ent_rows;             // most rows of an entry: RB_FINE or RB_ROWS
+  int32_t ent_ub;               // host upper bound of the entry count
+  int32_t r_max;
+  bool rank4;                   // every live rank is a multiple of 4
+  bool do_h, do_g;
+  const void* X;
+  int64_t ldx;
+  const void* dY;
+  int64_t lddy;
+  const float* H_saved;         // nullable: H is taken from here
+  int64_t ld_saved;
+  float* Hf;                    // nullable float32 rows of H, G
+  int64_t ldh;
+  float* Gf;
+  int64_t ldg;
+  uint16_t* fin;                // nullable (64-row entries): planes [H hi, H lo, G hi, G lo][j][column]
+  int32_t p_stride, r_pad;      // their row stride (elements) and rows
+};
+hipError_t launch_rowprod(const RowProdLaunch& l, hipStream_t s);
+// input gradient dX += s G A_a from G's float32 rows, over the entries o
+// describes (the plan's masked blocks)
+hipError_t launch_grad_x_mfma(const OpLaunch& o, const float* G, int64_t ldg, void* dX,
+                              lora_dtype dx_dtype, int64_t lddx, hipStream_t s);
 // plan-free small batch (lora_apply_ids): shrink per (slot, d-slice) into
 // partial planes H [slices][n][16 t] floats (t = 1, 2, 4 or 8 the rank tiles of
 // r_max), then expand per (slot, column chunk); every workgroup finds its
@@ -228,7 +255,7 @@ hipError_t launch_expand_valu(const OpLaunch& o, const float* H, int64_t ldh,
 
 // gradient path
 constexpr int GRAD_SLOT_GROUP = 64;   // output pointers passed per launch
-constexpr int GRAD_SPLITS_MAX = 8;    // most d-slices (partial planes) of the first stage
+constexpr int GRAD_SPLITS_MAX = 8;    // range of the policy's grad_splits field
 struct GradLaunch {
   OpLaunch o;                    // o.rb / o.rb_ub describe the trainable row blocks
   const int32_t* m_perm;
@@ -244,11 +271,11 @@ struct GradLaunch {
   float* const* dA;              // host array [num_slots] of device pointers (nullable entries)
   float* const* dB;
   int32_t accumulate;
-  float* hg;                     // workspace: partial H^T and G^T
-  int32_t k_splits;
+  float* hg;                     // workspace of the vector path: H^T and G^T
   int32_t p_stride;              // row stride (elements) of the H^T / G^T planes
   int32_t r_pad;                 // rank padding of the planes
-  uint16_t* fin;                 // workspace: summed planes, bf16 hi / lo
+  uint16_t* fin;                 // workspace of the matrix-core path: planes, bf16 hi / lo
+  bool rank4;                    // every live rank is a multiple of 4
 };
 
 // Byte offsets of the gradient workspace parts.
@@ -256,7 +283,10 @@ struct GradLayout {
   size_t partial, fin, total;
 };
 GradLayout grad_layout(int32_t mrb_ub, int32_t r_max);
-hipError_t launch_grad_mfma(const GradLaunch& g, hipStream_t s);
+// first stage (H and G as planes; Gf nullable: G's float32 rows too) and the
+// reduction over rows that reads it
+hipError_t launch_grad_hg_mfma(const GradLaunch& g, float* Gf, int64_t ldg, hipStream_t s);
+hipError_t launch_grad_dadb_mfma(const GradLaunch& g, hipStream_t s);
 hipError_t launch_grad_valu(const GradLaunch& g, lora_dtype x_dtype, lora_dtype w_dtype,
                             hipStream_t s);
 

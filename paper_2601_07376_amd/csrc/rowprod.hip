@@ -1,0 +1,347 @@
+// Row products of the bfloat16 matrix-core paths, for the rows of a plan's row
+// blocks:
+//
+//   H[t] = X[t] A_a^T   (A_a as stored, [r][d_in]:  K contiguous)
+//   G[t] = dY[t] B_a    (B_a as stored, [d_out][r]: the rank contiguous)
+//
+// Results go to float32 rows (the expand's operand) and / or to transposed
+// bfloat16 hi / lo planes [j][column] (the gradient's third stage), where row i
+// of block e sits in column 64 e + i.
+//
+// A unit is (R rows of a block, product) over the whole of K; the eight waves of
+// a workgroup take interleaved pieces of K and their sums meet in LDS in a fixed
+// order, so a row's result does not depend on R and no partial planes pass
+// through memory.  Rows stream from memory into registers in the matrix-core
+// layout, two batches in flight per wave.  A_a is read the same way; B_a's K rows
+// are one contiguous piece per batch, which goes straight into the wave's own
+// LDS area and is read back transposed (ds_read_b64_tr_b16).
+//
+// What bounds it: latency.  A unit resolves its rows through four dependent
+// reads (header, entry, row ids, rows) and then streams; the rows are read once
+// at 2 to 3 TB/s.  Against 64-row blocks cut into d-slices (four waves, B_a
+// gathered by 2-byte loads) and a second launch that summed the slices' planes,
+// both stages together: 2446 rows of 8 slots, 4096 -> 4096, rank 32: 20.8 ->
+// 20.1 us and one launch less; 4705 rows of 6 slots, 5120, rank 16, H saved:
+// 47.5 -> 34.2 us; a combined backward also no longer computes G twice.
+// More bytes in flight (four k-steps per batch instead of two) measured slower
+// (24.0 -> 25.9 us for G alone at 4705 rows).
+#include <algorithm>
+
+#include "device_common.h"
+#include "lora_internal.h"
+
+namespace lora {
+
+namespace {
+
+constexpr int RP_WAVES = 8, RP_T = RP_WAVES * 64;
+
+struct RpArgs {
+  RowProdLaunch l;
+  int32_t nprod;
+};
+
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+
+// (not a template: the host pass cannot resolve the builtin inside one)
+__device__ __forceinline__ void rp_dma16(rsrc_t src, uint8_t* lds, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16, off,
+                                           0, 0, 0);
+}
+__device__ __forceinline__ uint32_t rp_lds(const uint8_t* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p;
+}
+// Transposing read of a 32 (K) x 16 (rank) tile as a matrix-core operand: K rows
+// +0..3 at a0 and +4..7 at a1 of each 8-row group.  In asm with its wait: before
+// the builtin the compiler waits for every direct load in flight.  `after` is a
+// register of the batch's last row load: the compiler waits for it first, and
+// vector loads complete in order, so the batch's earlier direct loads are done.
+__device__ __forceinline__ bf16x8 rp_tr(uint32_t a0, uint32_t a1, uint32_t after) {
+  u32x4 v = {0u, 0u, 0u, 0u};
+#ifdef __HIP_DEVICE_COMPILE__
+  u32x2 p, q;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %2\n\t"
+      "ds_read_b64_tr_b16 %1, %3\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(p), "=&v"(q)
+      : "v"(a0), "v"(a1), "v"(after)
+      : "memory");
+  v = __builtin_shufflevector(p, q, 0, 1, 2, 3);
+#endif
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+template <int MT, int NT>
+struct Rp {
+  static constexpr int U = NT <= 2 && MT <= 2 ? 2 : 1;  // 32-wide k-steps per batch
+  static constexpr int SLOT = U * NT * 1024;            // a wave's staged weights of a batch
+  static constexpr int RING = RP_WAVES * 2 * SLOT;
+  static constexpr int PASS = 8;                        // accumulator tiles per reduction pass
+  static constexpr int RED = RP_WAVES * PASS * 1024;
+  static constexpr int LDS = RING > RED ? RING : RED;
+};
+
+// acc += rows W^T over this wave's pieces of [0, K).  G: W is [K][r], staged
+// through LDS; else [r][K], read directly.
+template <int MT, int NT, bool G, bool R4>
+__device__ __forceinline__ void rp_stream(f32x4 (&acc)[MT * NT], const uint16_t* (&xr)[MT], rsrc_t W,
+                                          int K, int r, uint8_t* ring) {
+  using P = Rp<MT, NT>;
+  constexpr int U = P::U;
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int kg = (lane >> 4) * 8, n = lane & 15;
+  uint8_t* const own = ring + w * 2 * P::SLOT;
+  struct Buf {
+    uint4 x[U][MT];
+    uint4 a[G ? 1 : U][G ? 1 : NT];
+  };
+  uint32_t wr[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int j = nt * 16 + n;
+    wr[nt] = (uint32_t)(j < r ? j : r - 1) * (uint32_t)K;
+  }
+  const int nb = (K + RP_WAVES * U * 32 - 1) / (RP_WAVES * U * 32);
+  auto load = [&](Buf& b, int bt, int slot) {
+    const int k0 = (bt * RP_WAVES + w) * (U * 32);
+    if constexpr (G) {
+#pragma unroll
+      for (int i = 0; i < U * NT; ++i)
+        rp_dma16(W, own + slot * P::SLOT + i * 1024,
+                 (uint32_t)k0 * (uint32_t)r * 2u + (uint32_t)(i * 1024 + lane * 16));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + u * 32 + kg, kk = k < K ? k : K - 8;
+      if constexpr (!G) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) b.a[u][nt] = bload16(W, (wr[nt] + (uint32_t)kk) * 2u);
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) b.x[u][mt] = ldg16(xr[mt] + kk);
+    }
+  };
+  auto mul = [&](const Buf& b, int bt, int slot) {
+    const int k0 = (bt * RP_WAVES + w) * (U * 32);
+    const uint8_t* sw = own + slot * P::SLOT;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool kv = k0 + u * 32 + kg < K;      // pieces past K are zeroed on the row operand
+      bf16x8 wv[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        if constexpr (!G) {
+          wv[nt] = as_bf16x8(b.a[u][nt]);
+        } else if constexpr (R4) {
+          const uint32_t at = rp_lds(sw) + (uint32_t)((u * 32 + kg + (n >> 2)) * r * 2 + nt * 32 + (n & 3) * 8);
+          wv[nt] = rp_tr(at, at + 8u * (uint32_t)r, b.x[U - 1][MT - 1].w);
+        } else {
+          // rank not a multiple of 4: K rows of odd length, read one by one
+          asm volatile("" ::"v"(b.x[U - 1][MT - 1].w) : "memory");
+          uint32_t e[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            e[i] = *reinterpret_cast<const uint16_t*>(sw + (u * 32 + kg + i) * r * 2 + (nt * 16 + n) * 2);
+          wv[nt] = pack_bf16x8(e);
+        }
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const bf16x8 xo = sel(kv, as_bf16x8(b.x[u][mt]));
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma_16x16x32(xo, wv[nt], acc[mt * NT + nt]);
+      }
+    }
+  };
+  // batches double buffered, the last one or two without loads behind them
+  Buf b0, b1;
+  load(b0, 0, 0);
+  int bt = 0;
+  for (; bt + 2 < nb; bt += 2) {
+    load(b1, bt + 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(b0, bt, 0);
+    load(b0, bt + 2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(b1, bt + 1, 1);
+    // wait states on the back edge between the last product and the loop
+    // head, where the compiler may read an accumulator register
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  load(b1, bt + 1, 1);               // (past the end: clamped, adds zeros)
+  __builtin_amdgcn_sched_barrier(0);
+  mul(b0, bt, 0);
+  mul(b1, bt + 1, 1);
+  mfma_fence();
+  // the direct loads have landed (the ring is reused next)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Four rows of rank column j of a block into the hi / lo planes `which` and
+// which + 1 (zero past the block's rows and the rank).
+__device__ __forceinline__ void rp_planes(const RowProdLaunch& l, const float (&v)[4], int which, int e,
+                                          int ib, int rows, int j, int r) {
+  float h[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) h[k] = ib + k < rows && j < r ? v[k] : 0.0f;
+  uint32_t hi[2], lo[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    hi[k] = pack2_bf16(h[2 * k], h[2 * k + 1]);
+    lo[k] = pack2_bf16(h[2 * k] - bf16_to_f32(hi[k] & 0xffffu),
+                       h[2 * k + 1] - bf16_to_f32(hi[k] >> 16));
+  }
+  uint16_t* d = l.fin + ((int64_t)(which * l.r_pad + j)) * l.p_stride + (int64_t)e * MRB_ROWS + ib;
+  *reinterpret_cast<uint2*>(d) = make_uint2(hi[0], hi[1]);
+  *reinterpret_cast<uint2*>(d + (int64_t)l.r_pad * l.p_stride) = make_uint2(lo[0], lo[1]);
+}
+
+// One unit: rows [i0, i0 + R) of a block of `rows` rows.
+template <int MT, int NT, bool R4>
+__device__ __forceinline__ void rp_unit(const RpArgs& p, const int4& en, int e, int i0, bool is_g,
+                                        uint8_t* lds) {
+  using P = Rp<MT, NT>;
+  constexpr int R = MT * 16, N = MT * NT;
+  const RowProdLaunch& l = p.l;
+  const int lane = threadIdx.x & 63, w = wave_id(), tid = threadIdx.x;
+  const int a = ck_slot(l.hdr, en.x, l.num_slots), p0 = en.y, rows = en.z;
+  const Slot m = load_slot(l.meta, a);
+  const int r = m.rank;
+  const bool saved = !is_g && l.H_saved != nullptr;
+  f32x4 acc[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // rows of the float32 outputs this thread stores in the first reduction
+  // pass, requested ahead of the products
+  float* const out = is_g ? l.Gf : l.Hf;
+  int orow[4] = {0, 0, 0, 0};
+  const int ob = i0 + ((tid >> 6) / NT) * 16 + (lane >> 4) * 4;
+  if (out != nullptr && i0 < rows) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) orow[k] = ck_row(l.hdr, l.perm[p0 + min(ob + k, rows - 1)], l.n);
+  }
+  if (i0 < rows && !saved) {
+    const uint16_t* xr[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int i = i0 + mt * 16 + (lane & 15);
+      const int t = ck_row(l.hdr, l.perm[p0 + min(i, rows - 1)], l.n);
+      xr[mt] = is_g ? static_cast<const uint16_t*>(l.dY) + (int64_t)t * l.lddy
+                    : static_cast<const uint16_t*>(l.X) + (int64_t)t * l.ldx;
+    }
+    if (is_g) {
+      const rsrc_t W = make_rsrc(m.B, (uint32_t)l.d_out * (uint32_t)r * 2u);
+      rp_stream<MT, NT, true, R4>(acc, xr, W, l.d_out, r, lds);
+    } else {
+      const rsrc_t W = make_rsrc(m.A, (uint32_t)l.d_in * (uint32_t)r * 2u);
+      rp_stream<MT, NT, false, R4>(acc, xr, W, l.d_in, r, lds);
+    }
+  }
+  if (saved) {
+    // H from the caller: one thread per rank column and four rows
+    for (int q = tid; q < R / 4 * l.r_pad; q += RP_T) {
+      const int g4 = q / l.r_pad, j = q - g4 * l.r_pad, ib = i0 + g4 * 4;
+      float h[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int t = ck_row(l.hdr, l.perm[p0 + min(ib + k, rows - 1)], l.n);
+        h[k] = l.H_saved[(int64_t)t * l.ld_saved + min(j, r - 1)];
+      }
+      rp_planes(l, h, 0, e, ib, rows, j, r);
+    }
+    return;
+  }
+  vmem_drained();
+  const int64_t ldo = is_g ? l.ldg : l.ldh;
+  f32x4* const red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+  for (int c0 = 0; c0 < N; c0 += P::PASS) {
+    constexpr int C = N < P::PASS ? N : P::PASS;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < C; ++i) red[(w * C + i) * 64 + lane] = acc[c0 + i];
+    __syncthreads();
+    for (int q = tid; q < C * 64; q += RP_T) {
+      f32x4 s[RP_WAVES];
+#pragma unroll
+      for (int k = 0; k < RP_WAVES; ++k) s[k] = red[k * C * 64 + q];
+      f32x4 v = ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
+      const int tile = c0 + (q >> 6), ln = q & 63;
+      const int mt = tile / NT, j = (tile - mt * NT) * 16 + (ln & 15);
+      const int ib = i0 + mt * 16 + (ln >> 4) * 4;         // rows ib .. ib + 3
+      if (out != nullptr && j < r) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (ib + k < rows) {
+            const int t = c0 == 0 ? orow[k] : ck_row(l.hdr, l.perm[p0 + ib + k], l.n);
+            out[(int64_t)t * ldo + j] = v[k];
+          }
+      }
+      if (l.fin != nullptr && j < l.r_pad) {
+        const float h[4] = {v[0], v[1], v[2], v[3]};
+        rp_planes(l, h, is_g ? 2 : 0, e, ib, rows, j, r);
+      }
+    }
+  }
+  __syncthreads();
+}
+
+template <int NT, bool R4>
+__global__ __launch_bounds__(RP_T, NT <= 2 ? 4 : 2) void rowprod_kernel(RpArgs p) {
+  __shared__ __align__(1024) uint8_t s_lds[Rp<1, NT>::LDS];
+  const RowProdLaunch& l = p.l;
+  const int count = l.hdr[l.count_word];
+  const int sub64 = l.ent_rows / 64;
+  const int np = p.nprod;
+  // Rows per unit.  Smaller ones re-read the weights from L2 more often (K r
+  // against K R elements per unit), larger ones leave CUs idle.  Whole lora_grad
+  // calls, with 16 / 32 / 64 rows per unit: 84 blocks of 64 (rank 32) 35.4 / 33.4 /
+  // 33.6 us, 152 blocks 58.1 / 60.3 / 59.2 (rank 16) and 123 / 110 / 99 (rank 64).
+  const int u64 = count * sub64 * np;
+  const int R = u64 >= 150 ? 64 : u64 >= 60 ? 32 : 16;
+  const int nsub = l.ent_rows / R;
+  // each XCD's share of the blocks: all of one product, then the other (in
+  // alternation, workgroups with next to nothing to do, as with a saved H, would
+  // fall on every other CU)
+  const XcdRange xr = xcd_range(count * nsub);
+  const int len = xr.end - xr.begin;
+  for (int u = xr.first - xr.begin; u < len * np; u += xr.step) {
+    const int wh = u / len, eq = xr.begin + u - wh * len;
+    const int e = eq / nsub, q = eq - e * nsub;
+    const bool is_g = np == 2 ? wh == 0 : l.do_g;
+    const int4 en = load_entry(l.ent, e);
+    if (q * R >= en.z && l.fin == nullptr) continue;
+    if (R == 64) rp_unit<4, NT, R4>(p, en, e, q * R, is_g, s_lds);
+    else if (R == 32) rp_unit<2, NT, R4>(p, en, e, q * R, is_g, s_lds);
+    else rp_unit<1, NT, R4>(p, en, e, q * R, is_g, s_lds);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_rowprod(const RowProdLaunch& l, hipStream_t s) {
+  RpArgs p{};
+  p.l = l;
+  p.nprod = (l.do_h ? 1 : 0) + (l.do_g ? 1 : 0);
+  if (l.ent_ub <= 0 || p.nprod == 0) return hipSuccess;
+  const long long units = (long long)l.ent_ub * (l.ent_rows / 16) * p.nprod;
+  const int grid = (int)((std::min<long long>(units, 2048) + 7) / 8 * 8);
+  const int nt = (l.r_max + 15) / 16;
+#define RPK(NT)                                                                                     \
+  do {                                                                                              \
+    if (l.rank4) hipLaunchKernelGGL((rowprod_kernel<NT, true>), dim3(grid), dim3(RP_T), 0, s, p);   \
+    else hipLaunchKernelGGL((rowprod_kernel<NT, false>), dim3(grid), dim3(RP_T), 0, s, p);          \
+  } while (0)
+  if (nt <= 1) RPK(1);
+  else if (nt <= 2) RPK(2);
+  else if (nt <= 4) RPK(4);
+  else RPK(8);
+#undef RPK
+  return hipGetLastError();
+}
+
+}  // namespace lora

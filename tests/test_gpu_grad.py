@@ -179,3 +179,47 @@ def test_grad_empty_batch():
     torch.cuda.synchronize()
     assert all(bool(torch.all(x == 0.0)) and not bool(torch.signbit(x).any())
                for x in dA + dB if x is not None)
+
+
+def check_exact(case, dA, dB):
+    X, A, B, _, dY = f64_case(case)
+    rA, rB = oracle.grad(effective(case), case.mask, X, dY, A, B, case.scales)
+    for a in range(case.num_slots):
+        if A[a] is None:
+            continue
+        assert np.array_equal(dA[a].cpu().double().numpy(), rA[a]), f"dA of slot {a}"
+        assert np.array_equal(dB[a].cpu().double().numpy(), rB[a]), f"dB of slot {a}"
+
+
+@pytest.mark.parametrize("rank", [8, 24, 48, 128])
+def test_grad_step_edges(rank):
+    """Trainable rows per slot around the 64-row step, the loads in flight and
+    the 2048-row window, in columns that end inside a tile.  Values in
+    {-1, 0, 1}: |H|, |G| <= 136 and |dA|, |dB| < 2^24, so every sum is exact and
+    the result must equal the oracle."""
+    say(f"grad step edges rank={rank}")
+    rows = [1, 63, 64, 65, 128, 129, 193, 2047, 2048, 2049, 4161]
+    S, n = len(rows) + 1, sum(rows) + 70            # the last slot has no trainable row
+    case = workloads.random_case(31 + rank, n, 136, 88, S, ranks=np.full(S, rank), frac_none=0.0,
+                                 want_dy=True, want_y=False, int_values=True, mask_p=0.5,
+                                 scales=np.array([0.5, 1.0, 2.0])[np.arange(S) % 3])
+    rng = np.random.default_rng(rank)
+    perm = rng.permutation(n)
+    case.idx = np.concatenate([np.repeat(np.arange(S), rows + [70])]).astype(np.int32)[perm]
+    case.mask = np.repeat([1, 0], [n - 70, 70]).astype(np.uint8)[perm]
+    check_exact(case, *run_grad(case))
+
+
+def test_grad_rows_past_two_gib():
+    """Row matrices of more than 2 GiB (views of wide buffers): the third
+    stage's loads take 64-bit addresses."""
+    say("grad rows past 2 GiB")
+    n, ld = 66000, 16640
+    case = workloads.random_case(77, n, 72, 40, 2, ranks=[16, 8], frac_none=0.0, layout="segments",
+                                 seg_len=(20000, 30000), want_dy=True, want_y=False,
+                                 int_values=True, mask_p=0.01, scales=[0.5, 2.0])
+    dev = case_to_device(case, DEV)
+    wide = torch.empty(n, ld, dtype=torch.bfloat16, device=DEV)
+    wide[:, :72], wide[:, 80:120] = dev["X"], dev["dY"]
+    plan = make_plan(case, dev, make_table(case, dev), mask=True)
+    check_exact(case, *L.grad(plan, wide[:, :72], wide[:, 80:120]))
