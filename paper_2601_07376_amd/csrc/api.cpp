@@ -679,6 +679,42 @@ void lora_plan_destroy(lora_plan* p) { delete p; }
 
 // ---- forward ---------------------------------------------------------------
 
+}  // extern "C"
+
+namespace {
+// Batches of so few 64-row blocks that the grouped shrink, which takes a block
+// per workgroup (and all of d_in, where the caller has room for one H only),
+// leaves most CUs idle.  lora_shrink, row products against grouped shrink:
+// 6001 rows (5120, rank 16) 17.9 / 27.1 us, rank 64 31.5 / 42.9; 8192 rows
+// (4096, rank 32) 33 / 26.7; 12000 rows about equal.
+bool use_rowprod(const lora_plan* p) { return p->fine && ub_fine(p) <= 112; }
+
+// H of every row with an adapter in one launch over the whole of d_in: all
+// entries (large-group blocks and small-group entries) of the plan
+lora::RowProdLaunch shrink_launch(const lora_plan* p, const void* X, int64_t ldx) {
+  lora::RowProdLaunch r{};
+  r.hdr = p->d.hdr;
+  r.ent = p->d.rb;
+  r.perm = p->d.perm;
+  r.meta = static_cast<const lora::SlotMeta*>(p->table->dev_meta);
+  r.n = p->n;
+  r.num_slots = p->table->num_slots;
+  r.d_in = p->table->d_in;
+  r.d_out = p->table->d_out;
+  r.count_word = lora::HDR_NRB_TOTAL;
+  r.ent_rows = p->fine ? lora::RB_FINE : lora::RB_ROWS;
+  r.ent_ub = (p->fine ? ub_fine(p) : ub_coarse(p)) + ub_small(p);
+  r.r_max = p->r_max;
+  r.rank4 = p->rank4;
+  r.do_h = true;
+  r.X = X;
+  r.ldx = ldx;
+  return r;
+}
+}  // namespace
+
+extern "C" {
+
 lora_status lora_shrink(const lora_plan* p, const void* X, lora_dtype x_dtype, int64_t ldx, float* H,
                         int64_t ldh, void* stream) {
   lora_status st = check_plan(p);
@@ -703,9 +739,14 @@ lora_status lora_shrink(const lora_plan* p, const void* X, lora_dtype x_dtype, i
   o.fine_ub = p->fine ? ub_fine(p) + ub_small(p) : 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
-  if (x_dtype == LORA_BF16 && t->w_dtype == LORA_BF16)
+  if (x_dtype == LORA_BF16 && t->w_dtype == LORA_BF16 && use_rowprod(p)) {
+    lora::RowProdLaunch r = shrink_launch(p, X, ldx);
+    r.Hf = H;
+    r.ldh = ldh;
+    e = lora::launch_rowprod(r, s);
+  } else if (x_dtype == LORA_BF16 && t->w_dtype == LORA_BF16) {
     e = lora::launch_shrink_mfma(o, X, ldx, H, ldh, 1, 0, s);
-  else
+  } else
     e = lora::launch_shrink_valu(o, X, x_dtype, ldx, t->w_dtype, H, ldh, s);
   if (e != hipSuccess) return hip_fail(e, "shrink launch");
   return ok();
@@ -1048,20 +1089,32 @@ lora_status lora_linear(const lora_plan* p, const void* X, lora_dtype x_dtype, i
   if (p->n == 0) return ok();
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t ldh = (std::max(p->r_max, 1) + 7) / 8 * 8;
-  const int64_t plane = (int64_t)(al256((size_t)std::max(p->n, 1) * ldh * 4) / 4);
   float* H = static_cast<float*>(ws);
   lora::OpLaunch o = op_base(p);
   hipError_t e = hipSuccess;
+  uint16_t* Hs = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + apply_h_bytes(p));
+  const int64_t plane = (int64_t)(al256((size_t)std::max(p->n, 1) * ldh * 4) / 4);
+  // batches of few 64-row blocks: s_a H packed in one launch (2003 rows, 5120 ->
+  // 5120, rank 16: 13.8 us against 11.4 + 4.9 for the d-sliced shrink and the
+  // packing of its planes; 15769 rows, 4096, rank 64: 80 against 41 + 15)
+  const bool packed = p->rank8 && use_rowprod(p);
   if (p->r_max > 0) {
-    // H of every row with an adapter (all entries: large-group blocks and
-    // small-group entries), in SHRINK_KS_MAX partial planes
-    lora::OpLaunch os = o;
-    os.count_word = lora::HDR_NRB_TOTAL;
-    os.first_word = -1;
-    os.rb_ub = ub_large(p) + ub_small(p);
-    os.coarse_ub = p->fine ? 0 : ub_coarse(p) + ub_small(p);
-    os.fine_ub = p->fine ? ub_fine(p) + ub_small(p) : 0;
-    e = lora::launch_shrink_mfma(os, X, ldx, H, ldh, lora::SHRINK_KS_MAX, plane, s);
+    if (packed) {
+      lora::RowProdLaunch r = shrink_launch(p, X, ldx);
+      r.Hs = Hs;
+      r.rp = lora::linear_rank_cols(p->r_max);
+      e = lora::launch_rowprod(r, s);
+    } else {
+      // H of every row with an adapter (all entries: large-group blocks and
+      // small-group entries), in SHRINK_KS_MAX partial planes
+      lora::OpLaunch os = o;
+      os.count_word = lora::HDR_NRB_TOTAL;
+      os.first_word = -1;
+      os.rb_ub = ub_large(p) + ub_small(p);
+      os.coarse_ub = p->fine ? 0 : ub_coarse(p) + ub_small(p);
+      os.fine_ub = p->fine ? ub_fine(p) + ub_small(p) : 0;
+      e = lora::launch_shrink_mfma(os, X, ldx, H, ldh, lora::SHRINK_KS_MAX, plane, s);
+    }
     if (e != hipSuccess) return hip_fail(e, "linear shrink launch");
   }
   lora::LinearLaunch l{};
@@ -1079,7 +1132,8 @@ lora_status lora_linear(const lora_plan* p, const void* X, lora_dtype x_dtype, i
   l.ldh = ldh;
   l.hp_stride = plane;
   l.ks_max = lora::SHRINK_KS_MAX;
-  l.Hs = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + apply_h_bytes(p));
+  l.packed = packed;
+  l.Hs = Hs;
   o.rb_ub = ub_large(p) + ub_small(p);
   e = lora::launch_linear_mfma(o, l, s);
   if (e != hipSuccess) return hip_fail(e, "linear launch");

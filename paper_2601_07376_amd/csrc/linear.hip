@@ -5,7 +5,8 @@
 //
 // The base projection is shared by every row and computed once for all of
 // them; the adapter residual is added per group, as the paper structures the
-// layer.  Two launches: the grouped shrink writes H = X A_a^T (float32, in
+// layer.  Two launches (the row products write s_a H as the GEMM reads it), or
+// three for long batches and ranks that are not multiples of 8: the grouped shrink writes H = X A_a^T (float32, in
 // d-sliced partial planes) for the rows of every adapter group; then one
 // matrix-core GEMM computes X W^T tile by tile and, before its store, adds
 // s_a H B_a^T for each maximal run of one adapter that crosses the tile, as
@@ -622,7 +623,7 @@ hipError_t launch_linear_mfma(const OpLaunch& o, const LinearLaunch& l, hipStrea
   const long long total = (long long)a.m_tiles * a.n_tiles;
   if (total <= 0) return hipSuccess;
   const int grid = (int)(8 * ((total + 7) / 8));
-  if (o.rank8 && o.r_max > 0 && o.rb_ub > 0) {
+  if (!l.packed && o.rank8 && o.r_max > 0 && o.rb_ub > 0) {
     hipLaunchKernelGGL(linear_hpack_kernel, dim3(std::min(o.rb_ub, 4096)), dim3(256), 0, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

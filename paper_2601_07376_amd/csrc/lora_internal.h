@@ -179,6 +179,8 @@ struct RowProdLaunch {
   int64_t ldh;
   float* Gf;
   int64_t ldg;
+  uint16_t* Hs;                 // nullable: s_a H as bf16 [row][hi rp | lo rp], zero past r_a
+  int32_t rp;
   uint16_t* fin;                // nullable (64-row entries): planes [H hi, H lo, G hi, G lo][j][column]
   int32_t p_stride, r_pad;      // their row stride (elements) and rows
 };
@@ -220,7 +222,8 @@ hipError_t launch_small_split_mfma(const OpLaunch& o, const void* X, int64_t ldx
 
 // the whole adapted layer Y = X W^T + s_a (X A_a^T) B_a^T (bf16 X, W and
 // weights): one GEMM whose epilogue adds the residual of every run crossing a
-// tile, from H = the grouped shrink's ks_max-sliced partial planes
+// tile, from the packed s_a H (ranks multiples of 8) or H = the grouped shrink's
+// ks_max-sliced partial planes
 struct LinearLaunch {
   const void* X;
   int64_t ldx;
@@ -236,6 +239,7 @@ struct LinearLaunch {
   int64_t ldh;
   int64_t hp_stride;
   int32_t ks_max;
+  bool packed;         // Hs is filled already (else it is filled from H)
   uint16_t* Hs;        // [n][2 linear_rank_cols(r_max)] bf16: the packed s_a H (rank multiple of 8)
 };
 int32_t linear_rank_cols(int32_t r_max);

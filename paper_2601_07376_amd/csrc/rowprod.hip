@@ -4,9 +4,10 @@
 //   H[t] = X[t] A_a^T   (A_a as stored, [r][d_in]:  K contiguous)
 //   G[t] = dY[t] B_a    (B_a as stored, [d_out][r]: the rank contiguous)
 //
-// Results go to float32 rows (the expand's operand) and / or to transposed
-// bfloat16 hi / lo planes [j][column] (the gradient's third stage), where row i
-// of block e sits in column 64 e + i.
+// Results go to float32 rows (the expand's operand), to rows of s_a H as
+// bfloat16 hi | lo (the whole layer's residual operand) and / or to transposed
+// hi / lo planes [j][column] (the gradient's reduction over rows), where row i of
+// block e sits in column 64 e + i.
 //
 // A unit is (R rows of a block, product) over the whole of K; the eight waves of
 // a workgroup take interleaved pieces of K and their sums meet in LDS in a fixed
@@ -218,9 +219,10 @@ __device__ __forceinline__ void rp_unit(const RpArgs& p, const int4& en, int e, 
   // rows of the float32 outputs this thread stores in the first reduction
   // pass, requested ahead of the products
   float* const out = is_g ? l.Gf : l.Hf;
+  const bool by_row = out != nullptr || l.Hs != nullptr;
   int orow[4] = {0, 0, 0, 0};
   const int ob = i0 + ((tid >> 6) / NT) * 16 + (lane >> 4) * 4;
-  if (out != nullptr && i0 < rows) {
+  if (by_row && i0 < rows) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) orow[k] = ck_row(l.hdr, l.perm[p0 + min(ob + k, rows - 1)], l.n);
   }
@@ -273,12 +275,20 @@ __device__ __forceinline__ void rp_unit(const RpArgs& p, const int4& en, int e, 
       const int tile = c0 + (q >> 6), ln = q & 63;
       const int mt = tile / NT, j = (tile - mt * NT) * 16 + (ln & 15);
       const int ib = i0 + mt * 16 + (ln >> 4) * 4;         // rows ib .. ib + 3
-      if (out != nullptr && j < r) {
+      if (by_row) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
           if (ib + k < rows) {
             const int t = c0 == 0 ? orow[k] : ck_row(l.hdr, l.perm[p0 + ib + k], l.n);
-            out[(int64_t)t * ldo + j] = v[k];
+            if (out != nullptr && j < r) out[(int64_t)t * ldo + j] = v[k];
+            if (l.Hs != nullptr && j < l.rp) {
+              const float h = j < r ? m.scale * v[k] : 0.0f;
+              const uint32_t hi = f32_to_bf16_rne(h);
+              uint16_t* d = l.Hs + (int64_t)t * (2 * l.rp) + j;
+              d[0] = (uint16_t)hi;
+              d[l.rp] = (uint16_t)f32_to_bf16_rne(h - bf16_to_f32(hi));
+              if (j + NT * 16 < l.rp) d[NT * 16] = d[l.rp + NT * 16] = 0;   // rank tiles rp pads to
+            }
           }
       }
       if (l.fin != nullptr && j < l.r_pad) {

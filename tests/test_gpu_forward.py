@@ -328,3 +328,28 @@ def test_apply_large_block_sizes(name, ydt):
     L.expand(plan, H, Y)
     torch.cuda.synchronize()
     check_forward(case, from_torch(Y), effective(case))
+
+
+@pytest.mark.parametrize("n", [1100, 2500, 7300])
+@pytest.mark.parametrize("d_in", [8, 72, 520, 1544])
+def test_shrink_row_products(n, d_in):
+    """H over the whole of d_in: batches around the sizes where the row products
+    change their rows per unit and where the grouped shrink takes over, ranks of
+    every residue mod 8 in one table, d_in shorter and longer than one batch of
+    loads.  Values in {-1, 0, 1}, |H| <= 1544: exact."""
+    say(f"shrink row products n={n} d_in={d_in}")
+    ranks = [1, 3, 4, 12, 16, 21, 24, 48, 126, 128]
+    for sub in (ranks, [4, 12, 16, 24]):
+        case = workloads.random_case(n + d_in, n, d_in, 16, len(sub), ranks=sub, layout="segments",
+                                     seg_len=(1, 500), int_values=True)
+        dev = case_to_device(case, DEV)
+        plan = make_plan(case, dev, make_table(case, dev), mask=False)
+        H = torch.full((n, 128), 7.0, device=DEV)
+        L.shrink(plan, dev["X"], H)
+        X, A, _, _, _ = f64_case(case)
+        H = H.cpu().double().numpy()
+        for a, r in enumerate(sub):
+            t = case.idx == a
+            assert np.array_equal(H[t, :r], X[t] @ A[a].T), f"slot {a}"
+            assert np.all(H[t, r:] == 7.0), "columns past the rank were written"
+        assert np.all(H[case.idx < 0] == 7.0), "rows with no adapter were written"
