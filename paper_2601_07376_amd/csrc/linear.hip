@@ -13,14 +13,31 @@
 // extra rank steps on the same accumulators (H enters the bfloat16 matrix core
 // as hi + lo terms).  The output Y is written once; nothing is read back.
 //
-// GEMM: 256 x 256 output tiles, 4 waves, each wave 128 x 128 as 4 x 4 tiles of
-// v_mfma_f32_32x32x16_bf16.  K advances 64 at a time: both operand tiles of a
-// step (256 rows of X and 256 rows of W, 64 bf16 each) go straight from global
-// memory into LDS (global_load_lds_dwordx4, no registers), double buffered, one
-// barrier per step.  Rows are stored 128 bytes apart with the eight 16-byte
-// chunks of row R permuted by XOR with f(R) = (R & 7) ^ ((R >> 3) & 1), so that
-// the 16 lanes of a fragment read (16 consecutive rows, one chunk) hit 16
-// distinct 16-byte bank groups.
+// GEMM: output tiles of 64 MB rows x 256 columns, 8 waves as 2 (rows) x 4
+// (columns) of 32 MB x 64, in tiles of v_mfma_f32_32x32x16_bf16.  K advances 64 at
+// a time: both operand tiles of a step go straight from global memory into LDS
+// (no registers), one step ahead of the one being multiplied.  Rows are stored
+// 128 bytes apart with the eight 16-byte chunks of row R permuted by XOR with
+// f(R) = (R & 7) ^ ((R >> 3) & 1), so that the 16 lanes of a fragment read (16
+// consecutive rows, one chunk) hit 16 distinct 16-byte bank groups.
+//
+// The two waves of a SIMD (w and w + 4) alternate: a sub-step of 16 K columns is
+// a phase of LDS reads and direct loads and a phase of products, a barrier after
+// each, and the second four waves run one phase behind the first four, so that
+// one wave's memory instructions issue while the other's products run.  With four
+// waves of 128 x 128 (one per SIMD) the products waited for them: timing copies of
+// that kernel put the 15769 x 4096 -> 14336 layer at 1606 us, 1298 without the
+// direct loads, 1535 without the LDS reads, 1551 with the loads from L2 only,
+// 1217 without either.  This form takes 1496 (two waves per SIMD in step: 1571;
+// 32-column steps four or five deep: 1588; raised wave priority in the product
+// phases: no change; 1415 in a copy without the LDS reads): what is left is the
+// issue of the direct loads.
+//
+// Phases: p = 2 (4 step + sub) and one more for the second half.  The last reads
+// of step k end before phase 8 (k + 1) in both halves, so loads into its slot
+// (step k + 2, issued in the first two sub-steps of step k + 1) cannot overtake
+// them; every wave waits for its loads of step k + 1 in its last memory phase of
+// step k, at the latest in phase 8 k + 7, one barrier before any wave reads them.
 //
 // Matrix core: lane l holds row l % 32 of the A operand and column l % 32 of
 // the B operand, eight consecutive K values at K offset 8 (l / 32); the 16
@@ -33,23 +50,18 @@
 
 namespace lora {
 
-#ifndef LINEAR_KS
-#define LINEAR_KS 64
-#define LINEAR_NS 2
-#define LINEAR_NTS 1
-#define LINEAR_DMA 1
-#endif
-
 namespace {
 
-constexpr int LT_M = 256, LT_N = 256;
+constexpr int LT_N = 256;                       // tile columns; its rows are 64 MB
+constexpr int KS = 64;                          // K columns per step
+constexpr int NS = 2;                           // steps in LDS
+constexpr bool NTS = true;                      // non-temporal stores of Y
 constexpr int LT_GM = 4;                        // row tiles per group of the tile order
-constexpr int LT_SST = 132;                     // row stride (floats) of the store staging
+constexpr int LT_SST = 68;                      // row stride (floats) of the store staging
+constexpr int LT_W = 8;                         // waves, 2 (rows) x 4 (columns) of 128 x 64
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// instruction classes of __builtin_amdgcn_sched_group_barrier
-constexpr int SG_MFMA = 0x008, SG_VMEM = 0x010, SG_DS_READ = 0x100;
 
 struct LinArgs {
   const uint16_t* X;
@@ -81,46 +93,40 @@ __device__ __forceinline__ f32x16 mfma_32x32x16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// Staging of one K step of KS columns: every operand row is KS bf16 = KS / 8
-// chunks of 16 bytes, chunk c of row R stored at physical chunk c ^ f(R), so
-// that the 16 lanes of a fragment read (16 consecutive rows, one chunk) hit 16
-// distinct 16-byte bank groups: KS = 64 (128-byte rows, 2 rows per 256 bytes):
-// f(R) = (R & 7) ^ ((R >> 3) & 1); KS = 32 (64-byte rows): f(R) = (R >> 2) & 3.
-template <int KS>
+// Staging of one K step: every operand row is 64 bf16 = 8 chunks of 16 bytes,
+// chunk c of row R stored at physical chunk c ^ f(R), f(R) = (R & 7) ^ ((R >> 3) & 1).
+// ROWS: the operand's rows, 64 MB of X or 256 of W.
+template <int ROWS>
 struct Stage {
   static constexpr int ROW = KS * 2;                 // bytes per staged row
   static constexpr int CH = KS / 8;                  // chunks per row
-  static constexpr int OP = LT_M * ROW;              // bytes per operand tile
+  static constexpr int OP = ROWS * ROW;              // bytes of the operand tile
   static constexpr int RPI = 1024 / ROW;             // rows per direct load (1 KB per wave)
-  static constexpr int IPW = LT_M / RPI / 4;         // direct loads per wave and operand
-  static constexpr int SUB = KS / 16;                // matrix-core sub-steps
-  __device__ static __forceinline__ int swz(int row) {
-    return KS == 64 ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3);
-  }
+  static constexpr int IPW = ROWS / RPI / LT_W;      // direct loads per wave
 };
+__device__ __forceinline__ int lt_swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
 // Per-lane source offsets of one operand's direct loads.  Load i of wave w
 // fills LDS bytes [(IPW w + i) 1024, +1024): row R = (IPW w + i) RPI + lane / CH,
-// physical chunk lane % CH, so logical chunk (lane % CH) ^ f(R).  For both
-// staging widths that chunk depends on the lane and on i & 1 only, and the rows
-// of load i are RPI i past those of load 0 (a wave-uniform step, which goes into
-// the scalar offset with the step's K).
-template <int KS>
+// physical chunk lane % CH, so logical chunk (lane % CH) ^ f(R).  That chunk
+// depends on the lane, the wave and i & 1 only, and the rows of load i are RPI i
+// past those of load 0 (a wave-uniform step, which goes into the scalar offset
+// with the step's K).
 struct StageMap {
   uint32_t off[2];     // lane offset at k = 0 for even / odd i
   int chunk[2];
   uint32_t step;       // bytes of RPI rows
 };
 
-template <int KS>
-__device__ __forceinline__ StageMap<KS> lt_map(int64_t ld, int w, int lane) {
-  using S = Stage<KS>;
-  StageMap<KS> m;
+template <int ROWS>
+__device__ __forceinline__ StageMap lt_map(int64_t ld, int w, int lane) {
+  using S = Stage<ROWS>;
+  StageMap m;
   m.step = (uint32_t)S::RPI * (uint32_t)ld * 2u;
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     const int row = (S::IPW * w + e) * S::RPI + lane / S::CH;
-    m.chunk[e] = (lane % S::CH) ^ S::swz(row);
+    m.chunk[e] = (lane % S::CH) ^ lt_swz(row);
     m.off[e] = (uint32_t)(row - e * S::RPI) * (uint32_t)ld * 2u + (uint32_t)m.chunk[e] * 16u;
   }
   return m;
@@ -141,80 +147,50 @@ __device__ __forceinline__ void lt_st16(rsrc_t dst, u32x4 v, uint32_t voff, bool
   else __builtin_amdgcn_raw_buffer_store_b128(v, dst, voff, 0, 0);
 }
 
-// One 16-byte load per lane into registers (the staging-through-registers path).
-__device__ __forceinline__ u32x4 lt_ld16(rsrc_t src, uint32_t voff, uint32_t soff) {
-  return __builtin_amdgcn_raw_buffer_load_b128(src, voff, soff, 0);
-}
-
-// Where the loads of one K step go: straight into LDS (DMA), or into the
-// registers R (2 IPW per lane) to be written to LDS one step later.
-template <int KS, bool DMA>
-struct Sink {
-  u32x4 (&R)[2 * Stage<KS>::IPW];
-  __device__ __forceinline__ void put(int k, rsrc_t src, uint8_t* lds, uint32_t voff, uint32_t soff) {
-    if (DMA) lt_dma16(src, lds, voff, soff);
-    else R[k] = lt_ld16(src, voff, soff);
-  }
-};
-
-// Registers of one K step into its LDS slot: load k of wave w sits at bytes
-// (IPW w + k) 1024 + 16 lane of the A tile (k < IPW) or the B tile.
-template <int KS>
-__device__ __forceinline__ void lt_write(const u32x4 (&R)[2 * Stage<KS>::IPW], uint8_t* slot, int w,
-                                         int lane) {
-  using S = Stage<KS>;
-#pragma unroll
-  for (int k = 0; k < 2 * S::IPW; ++k) {
-    uint8_t* d = slot + (k < S::IPW ? 0 : S::OP) + (S::IPW * w + (k % S::IPW)) * 1024 + lane * 16;
-    *reinterpret_cast<u32x4*>(d) = R[k];
-  }
-}
-
 // One operand tile of one K step into LDS, through a buffer resource whose base
 // is the tile's first row and whose size covers its valid rows: offsets past
 // it read zeros (the rows past n or d_out of the last tiles), and chunks past
 // d_in are sent past it (the K tail reads zeros).
-template <int KS, bool DMA>
-__device__ __forceinline__ void lt_stage(Sink<KS, DMA> sk, int k_base, const uint16_t* base,
-                                         uint32_t bytes, const StageMap<KS>& m, int k0, int d_in,
-                                         uint8_t* lds, int w) {
-  using S = Stage<KS>;
+template <int ROWS>
+__device__ __forceinline__ void lt_stage(const uint16_t* base, uint32_t bytes, const StageMap& m, int k0,
+                                         int d_in, uint8_t* lds, int w) {
+  using S = Stage<ROWS>;
   const rsrc_t src = make_rsrc(base, bytes);
   const int left = d_in - k0;          // valid K columns from k0 on
   const uint32_t v0 = 8 * m.chunk[0] < left ? m.off[0] : 0x80000000u;
   const uint32_t v1 = 8 * m.chunk[1] < left ? m.off[1] : 0x80000000u;
 #pragma unroll
   for (int i = 0; i < S::IPW; ++i)
-    sk.put(k_base + i, src, lds + (S::IPW * w + i) * 1024, (i & 1) ? v1 : v0,
-           (uint32_t)k0 * 2u + (uint32_t)i * m.step);
+    lt_dma16(src, lds + (S::IPW * w + i) * 1024, (i & 1) ? v1 : v0,
+             (uint32_t)k0 * 2u + (uint32_t)i * m.step);
 }
 
-template <int KS>
 __device__ __forceinline__ bf16x8 lt_frag(const uint8_t* lds, int row, int chunk) {
-  using S = Stage<KS>;
-  return *reinterpret_cast<const bf16x8*>(lds + row * S::ROW + ((chunk ^ S::swz(row)) << 4));
+  return *reinterpret_cast<const bf16x8*>(lds + row * (KS * 2) + ((chunk ^ lt_swz(row)) << 4));
 }
 
-// Fragments of one 16-wide K sub-step: 4 A (rows) and 4 B (columns) per wave.
+// Fragments of one 16-wide K sub-step: MB A (rows) and 2 B (columns) per wave.
+template <int MB>
 struct Frags {
-  bf16x8 a[4], b[4];
+  bf16x8 a[MB], b[2];
 };
 
-template <int KS>
-__device__ __forceinline__ void lt_read(Frags& f, const uint8_t* sa, const uint8_t* sb, int kk,
+template <int MB>
+__device__ __forceinline__ void lt_read(Frags<MB>& f, const uint8_t* sa, const uint8_t* sb, int kk,
                                         int wm, int wn, int lane) {
   const int rl = lane & 31, ch = lane >> 5;
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) f.a[mb] = lt_frag<KS>(sa, wm * 128 + mb * 32 + rl, 2 * kk + ch);
+  for (int mb = 0; mb < MB; ++mb) f.a[mb] = lt_frag(sa, (wm * MB + mb) * 32 + rl, 2 * kk + ch);
 #pragma unroll
-  for (int nb = 0; nb < 4; ++nb) f.b[nb] = lt_frag<KS>(sb, wn * 128 + nb * 32 + rl, 2 * kk + ch);
+  for (int nb = 0; nb < 2; ++nb) f.b[nb] = lt_frag(sb, wn * 64 + nb * 32 + rl, 2 * kk + ch);
 }
 
-__device__ __forceinline__ void lt_mma(const Frags& f, f32x16 (&acc)[4][4]) {
+template <int MB>
+__device__ __forceinline__ void lt_mma(const Frags<MB>& f, f32x16 (&acc)[MB][2]) {
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mfma_32x32x16(f.a[mb], f.b[nb], acc[mb][nb]);
+    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = mfma_32x32x16(f.a[mb], f.b[nb], acc[mb][nb]);
 }
 
 // Wait until at most N of this wave's vector memory operations are
@@ -232,32 +208,35 @@ __device__ __forceinline__ void lt_barrier() {
 // step read at rank column (j KS + k') mod rp (hi and lo halves meet the same
 // B_a), zero past r_a.  Rank a multiple of 8, so every 16-byte chunk of a B_a
 // row is aligned and lies wholly inside or outside [0, r_a).
-template <int KS, bool DMA>
-__device__ __forceinline__ void lt_stage_lora(Sink<KS, DMA> sk, const LinArgs& p, const StageMap<KS>& hm,
-                                              int r0, int n0, int j, int rs, int re, const uint16_t* Ba,
-                                              int r, uint8_t* lds, int w, int lane) {
-  using S = Stage<KS>;
+template <int MB>
+__device__ __forceinline__ void lt_stage_lora_h(const LinArgs& p, const StageMap& hm, int r0, int j, int rs,
+                                                int re, uint8_t* lds, int w, int lane) {
+  using S = Stage<64 * MB>;
   const rsrc_t ha = make_rsrc(p.Hs + (int64_t)r0 * (2 * p.rp),
-                              (uint32_t)min(LT_M, p.n - r0) * (uint32_t)(2 * p.rp) * 2u);
+                              (uint32_t)min(64 * MB, p.n - r0) * (uint32_t)(2 * p.rp) * 2u);
+#pragma unroll
+  for (int i = 0; i < S::IPW; ++i) {
+    const int row = (S::IPW * w + i) * S::RPI + lane / S::CH;
+    const bool in = r0 + row >= rs && r0 + row <= re;
+    lt_dma16(ha, lds + (S::IPW * w + i) * 1024, in ? hm.off[i & 1] : 0x80000000u,
+             (uint32_t)(j * KS) * 2u + (uint32_t)i * hm.step);
+  }
+}
+__device__ __forceinline__ void lt_stage_lora_b(const LinArgs& p, const StageMap& wm, int n0, int j,
+                                                const uint16_t* Ba, int r, uint8_t* lds, int w, int lane) {
+  using S = Stage<LT_N>;
   const rsrc_t bb = make_rsrc(Ba + (int64_t)n0 * r, (uint32_t)min(LT_N, p.d_out - n0) * (uint32_t)r * 2u);
   const int lr = lane / S::CH;                         // row of load i: (IPW w + i) RPI + lr
   uint32_t bo[2];
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const int jj = (j * KS + 8 * hm.chunk[e]) % p.rp;
+    const int jj = (j * KS + 8 * wm.chunk[e]) % p.rp;
     bo[e] = jj < r ? ((uint32_t)lr * (uint32_t)r + (uint32_t)jj) * 2u : 0x80000000u;
   }
 #pragma unroll
-  for (int i = 0; i < S::IPW; ++i) {
-    const int row = (S::IPW * w + i) * S::RPI + lr;
-    const bool in = r0 + row >= rs && r0 + row <= re;
-    sk.put(i, ha, lds + (S::IPW * w + i) * 1024, in ? hm.off[i & 1] : 0x80000000u,
-           (uint32_t)(j * KS) * 2u + (uint32_t)i * hm.step);
-  }
-#pragma unroll
   for (int i = 0; i < S::IPW; ++i)
-    sk.put(S::IPW + i, bb, lds + S::OP + (S::IPW * w + i) * 1024, bo[i & 1],
-           (uint32_t)((S::IPW * w + i) * S::RPI) * (uint32_t)r * 2u);
+    lt_dma16(bb, lds + (S::IPW * w + i) * 1024, bo[i & 1],
+             (uint32_t)((S::IPW * w + i) * S::RPI) * (uint32_t)r * 2u);
 }
 
 // Packs the residual's left operand once per call: for every row t of an
@@ -314,31 +293,28 @@ __device__ __forceinline__ bool lt_tile(const LinArgs& p, int& m, int& nt) {
   return true;
 }
 
-// KS: K columns per step; NS: steps staged in LDS at once; NTS: non-temporal
-// stores of Y; DMA: operands go straight from memory to LDS (NS - 1 steps in
-// flight while one is multiplied), else through registers (NS = 2: one step in
-// LDS being multiplied, the next in LDS, the one after in registers).
-template <bool YBF16, bool RANK8, int KS, int NS, bool NTS, bool DMA>
-__global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
-  using S = Stage<KS>;
-  static_assert(DMA || NS == 2, "register staging keeps two LDS slots");
-  // ring of NS steps, each [A | B][256 rows x S::ROW bytes]
-  constexpr int BUFB = 2 * S::OP;
+template <bool YBF16, bool RANK8, int MB>
+__global__ __launch_bounds__(LT_W * 64, 2) void linear_kernel(LinArgs p) {
+  using SA = Stage<64 * MB>;
+  using SB = Stage<LT_N>;
+  constexpr int LT_M = 64 * MB;
+  // ring of NS steps, each [64 MB rows of X | 256 rows of W] x 128 bytes
+  constexpr int BUFB = SA::OP + SB::OP;
   static_assert(NS * BUFB <= 160 * 1024, "LDS");
-  static_assert(NS * BUFB >= 4 * 32 * LT_SST * 4, "store staging fits in the ring");
+  static_assert(NS * BUFB >= LT_W * 32 * LT_SST * 4, "store staging fits in the ring");
   __shared__ __align__(1024) uint8_t s_lds[NS * BUFB];
   int m, nt;
   if (!lt_tile(p, m, nt)) return;
   const int lane = threadIdx.x & 63, w = wave_id();
-  const int wm = w >> 1, wn = w & 1;
+  const int wm = w >> 2, wn = w & 3;
   const int rl = lane & 31, ch = lane >> 5;
   const int r0 = m * LT_M, n0 = nt * LT_N;
 
-  f32x16 acc[4][4];
+  f32x16 acc[MB][2];
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+    for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.0f;
 
@@ -348,18 +324,10 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
   const uint32_t xb = (uint32_t)min(LT_M, p.n - r0) * (uint32_t)p.ldx * 2u;
   const uint16_t* ws = p.W + (int64_t)n0 * p.ldw;
   const uint32_t wb = (uint32_t)min(LT_N, p.d_out - n0) * (uint32_t)p.ldw * 2u;
-  const StageMap<KS> xm = lt_map<KS>(p.ldx, w, lane), wmap = lt_map<KS>(p.ldw, w, lane);
-  // Pipeline: steps 0 .. NS - 1 are requested up front.  Step ks multiplies
-  // ring slot ks % NS in SUB sub-steps, each reading the next sub-step's
-  // fragments into the other register set before its own products.  After the
-  // reads of the last sub-step the wave waits for step ks + 1's loads (steps
-  // ks + 2 .. ks + NS - 1 may still be in flight) and meets the others at the
-  // barrier (every wave has then read all of slot ks % NS); it requests step
-  // ks + NS into that slot and reads step ks + 1's first sub-step, and only
-  // then runs the products of the last sub-step, which cover the barrier and
-  // the read latency.  Loads past the last step read zeros into slots nobody
-  // reads, so no memory operation sits behind a branch.
-  constexpr int LPS = 2 * S::IPW;                // direct loads per wave and step
+  const StageMap xm = lt_map<64 * MB>(p.ldx, w, lane), wmap = lt_map<LT_N>(p.ldw, w, lane);
+  // Pipeline: see the head of the file.  Loads past the last step read zeros into
+  // slots nobody reads, so no memory operation sits behind a branch.
+  constexpr int LPS = SA::IPW + SB::IPW;         // direct loads per wave and step
   // Step sequence: the nk steps of X W^T, then (rank a multiple of 8) spr steps
   // per run of one adapter crossing the tile, which add s_a H B_a^T to the same
   // accumulators; past the end, steps read zeros.
@@ -376,15 +344,14 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
     while (k_first + nrt < nr && uni(p.run_start[k_first + nrt]) < r0 + LT_M) ++nrt;
   }
   const int T = nk + nrt * p.spr;
-  const StageMap<KS> hm = lt_map<KS>(2 * p.rp, w, lane);
+  const StageMap hm = lt_map<64 * MB>(2 * p.rp, w, lane);
   int cur_run = -1, rs = 0, re = -1, rr = 8;
   const uint16_t* Ba = p.W;
-  u32x4 R[2 * S::IPW];
-  const Sink<KS, DMA> sk{R};
-  auto issue = [&](int st, uint8_t* dst) {
+  // loads of step st: the X (or H) half, then the W (or B_a) half
+  auto issue = [&](int st, uint8_t* dst, int half) {
     if (st < nk || st >= T) {
-      lt_stage(sk, 0, xs, xb, xm, st * KS, p.d_in, dst, w);
-      lt_stage(sk, S::IPW, ws, wb, wmap, st * KS, p.d_in, dst + S::OP, w);
+      if (half == 0) lt_stage<64 * MB>(xs, xb, xm, st * KS, p.d_in, dst, w);
+      else lt_stage<LT_N>(ws, wb, wmap, st * KS, p.d_in, dst + SA::OP, w);
     } else {
       const int q = st - nk, kr = q / p.spr;
       if (kr != cur_run) {
@@ -395,80 +362,48 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
         Ba = static_cast<const uint16_t*>(sm.B);
         rr = sm.rank;
       }
-      lt_stage_lora(sk, p, hm, r0, n0, q - kr * p.spr, rs, re, Ba, rr, dst, w, lane);
+      const int j = q - kr * p.spr;
+      if (half == 0) lt_stage_lora_h<MB>(p, hm, r0, j, rs, re, dst, w, lane);
+      else lt_stage_lora_b(p, wmap, n0, j, Ba, rr, dst + SA::OP, w, lane);
     }
   };
-  if (DMA) {
 #pragma unroll
-    for (int j = 0; j < NS; ++j) issue(j, s_lds + j * BUFB);
-    lt_barrier<(NS - 1) * LPS>();
-  } else {
-    issue(0, s_lds);
-    lt_write<KS>(R, s_lds, w, lane);
-    issue(1, s_lds + BUFB);
-    lt_barrier<LPS>();
+  for (int j = 0; j < NS - 1; ++j) {
+    issue(j, s_lds + j * BUFB, 0);
+    issue(j, s_lds + j * BUFB, 1);
   }
-  Frags f0, f1;
-  lt_read<KS>(f0, s_lds, s_lds + S::OP, 0, wm, wn, lane);
-  // one step: its products, with the loads of step ks + NS (ks + 2 through
-  // the registers) issued at its end through `load`
+  lt_barrier<(NS - 2) * LPS>();
+  const bool second = w >= LT_W / 2;
+  if (second) asm volatile("s_barrier" ::: "memory");
+  int slot = 0;
+  Frags<MB> f;
   auto step = [&](int ks, auto load) {
-    const int slot = ks % NS;
     uint8_t* cur = s_lds + slot * BUFB;
-    uint8_t* nxt = s_lds + (slot + 1 == NS ? 0 : slot + 1) * BUFB;
+    uint8_t* prv = s_lds + (slot == 0 ? NS - 1 : slot - 1) * BUFB;
 #pragma unroll
-    for (int kk = 0; kk + 1 < S::SUB; ++kk) {
-      lt_read<KS>((kk & 1) ? f0 : f1, cur, cur + S::OP, kk + 1, wm, wn, lane);
-      lt_mma((kk & 1) ? f1 : f0, acc);
-      // one fragment read after each of the first 8 products, so the reads
-      // issue while the matrix core is busy
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(SG_MFMA, 8, 0);
+    for (int kk = 0; kk < KS / 16; ++kk) {
+      lt_read<MB>(f, cur, cur + SA::OP, kk, wm, wn, lane);
+      if (kk == 0) load(ks + NS - 1, prv, 0);
+      if (kk == 1) load(ks + NS - 1, prv, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (kk + 1 == KS / 16) lt_barrier<(NS - 2) * LPS>();
+      else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      lt_mma<MB>(f, acc);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (DMA) {
-      lt_barrier<(NS - 2) * LPS>();
-      load(ks + NS, cur);
-    } else {
-      // step ks + 1 from the registers into the other slot (last read in step
-      // ks - 1, before the previous barrier), then step ks + 2 into the
-      // registers; the barrier waits for the writes, not for those loads
-      lt_write<KS>(R, nxt, w, lane);
-      load(ks + 2, nxt);
-      lt_barrier<LPS>();
-    }
-    lt_read<KS>(f0, nxt, nxt + S::OP, 0, wm, wn, lane);
-    lt_mma(f1, acc);           // the last sub-step (SUB is even: its fragments are in f1)
-    if (DMA) {
-      // the step's loads two per product, then the next step's first reads one
-      // per product: the matrix core stays busy while they issue
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(SG_VMEM, LPS / 8, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    slot = slot + 1 == NS ? 0 : slot + 1;
   };
-  // steps whose loads are all of X W^T run without a branch in the loop body;
-  // the rest (the last steps of X W^T and the run steps) take the general loader
-  const int lead = DMA ? NS : 2;
-  const int n_plain = max(0, nk - lead);
-  auto plain = [&](int st, uint8_t* dst) {
-    lt_stage(sk, 0, xs, xb, xm, st * KS, p.d_in, dst, w);
-    lt_stage(sk, S::IPW, ws, wb, wmap, st * KS, p.d_in, dst + S::OP, w);
+  const int n_plain = max(0, nk - (NS - 1));
+  auto plain = [&](int st, uint8_t* dst, int half) {
+    if (half == 0) lt_stage<64 * MB>(xs, xb, xm, st * KS, p.d_in, dst, w);
+    else lt_stage<LT_N>(ws, wb, wmap, st * KS, p.d_in, dst + SA::OP, w);
   };
   for (int ks = 0; ks < n_plain; ++ks) step(ks, plain);
   for (int ks = n_plain; ks < T; ++ks) step(ks, issue);
+  if (!second) asm volatile("s_barrier" ::: "memory");
 
   // ---- ranks not a multiple of 8: + s_a H B_a^T for each run crossing the
   // tile, from the slice planes, after the main loop --------------------------
@@ -490,15 +425,15 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
     const rsrc_t Bw = make_rsrc(sm.B, (uint32_t)p.d_out * (uint32_t)r * 2u);
     for (int j0 = 0; j0 < r; j0 += 16) {
       const int jj = j0 + 8 * ch;
-      bf16x8 bo[4];
+      bf16x8 bo[2];
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        const int o = min(n0 + wn * 128 + nb * 32 + rl, p.d_out - 1);
+      for (int nb = 0; nb < 2; ++nb) {
+        const int o = min(n0 + wn * 64 + nb * 32 + rl, p.d_out - 1);
         bo[nb] = sel(jj < r, wrow8<RANK8>(Bw, (uint32_t)o * (uint32_t)r, jj, r));
       }
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        const int row = r0 + wm * 128 + mb * 32 + rl;
+      for (int mb = 0; mb < MB; ++mb) {
+        const int row = r0 + (wm * MB + mb) * 32 + rl;
         const bool in = row >= rs && row <= re;
         const int rc = min(max(row, rs), re);
         float h[8];
@@ -521,7 +456,7 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
         bf16x8 hh, hl;
         split_hi_lo(h, hh, hl);
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
+        for (int nb = 0; nb < 2; ++nb) {
           acc[mb][nb] = mfma_32x32x16(hh, bo[nb], acc[mb][nb]);
           acc[mb][nb] = mfma_32x32x16(hl, bo[nb], acc[mb][nb]);
         }
@@ -532,10 +467,10 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
   mfma_fence();
 
   // ---- store -----------------------------------------------------------------
-  // One 32-row block of the wave's 128 x 128 at a time through the wave's own
-  // LDS area (32 rows of 128 floats, stride LT_SST), then back as 16-byte
-  // vectors of whole rows: each store instruction writes four 256-byte row
-  // pieces (bfloat16) or two 512-byte ones (float32).  The stores go through a
+  // One 32-row block of the wave's 32 MB x 64 at a time through the wave's own
+  // LDS area (32 rows of 64 floats, stride LT_SST), then back as 16-byte
+  // vectors of whole rows: each store instruction writes eight 128-byte row
+  // pieces (bfloat16) or four 256-byte ones (float32).  The stores go through a
   // resource covering the tile's valid rows, with columns past d_out sent past
   // it, so none sits behind a branch.
   lt_barrier<0>();     // the unused loads past the last step have landed; all LDS reads done
@@ -544,21 +479,21 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
   const rsrc_t yr = make_rsrc(static_cast<char*>(p.Y) + ((int64_t)r0 * p.ldy + n0) * ES,
                               (uint32_t)min(LT_M, p.n - r0) * (uint32_t)p.ldy * ES);
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
+  for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+    for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int v = 0; v < 16; ++v)
         st[(8 * (v >> 2) + 4 * ch + (v & 3)) * LT_SST + nb * 32 + rl] = acc[mb][nb][v];
-    const int row_base = wm * 128 + mb * 32;       // tile-local
+    const int row_base = (wm * MB + mb) * 32;       // tile-local
     if (YBF16) {
-      // lane: row 4 q + lane / 16 of each group of 4 rows, columns 8 (lane % 16) ..
-      const int c8 = wn * 128 + (lane & 15) * 8;
+      // lane: row 8 q + lane / 8 of each group of 8 rows, columns 8 (lane % 8) ..
+      const int c8 = wn * 64 + (lane & 7) * 8;
       const bool col_ok = n0 + c8 < p.d_out;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int rr = 4 * q + (lane >> 4);
-        const float* sp = st + rr * LT_SST + (lane & 15) * 8;
+      for (int q = 0; q < 4; ++q) {
+        const int rr = 8 * q + (lane >> 3);
+        const float* sp = st + rr * LT_SST + (lane & 7) * 8;
         const float4 a0 = *reinterpret_cast<const float4*>(sp);
         const float4 a1 = *reinterpret_cast<const float4*>(sp + 4);
         const u32x4 o = {pack2_bf16(a0.x, a0.y), pack2_bf16(a0.z, a0.w),
@@ -568,12 +503,12 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
         lt_st16(yr, o, off, NTS);
       }
     } else {
-      const int c4 = wn * 128 + (lane & 31) * 4;
+      const int c4 = wn * 64 + (lane & 15) * 4;
       const bool col_ok = n0 + c4 < p.d_out;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int rr = 2 * q + (lane >> 5);
-        const float4 a = *reinterpret_cast<const float4*>(st + rr * LT_SST + (lane & 31) * 4);
+      for (int q = 0; q < 8; ++q) {
+        const int rr = 4 * q + (lane >> 4);
+        const float4 a = *reinterpret_cast<const float4*>(st + rr * LT_SST + (lane & 15) * 4);
         const u32x4 o = {__float_as_uint(a.x), __float_as_uint(a.y), __float_as_uint(a.z),
                          __float_as_uint(a.w)};
         const uint32_t off = col_ok ? ((uint32_t)(row_base + rr) * (uint32_t)p.ldy + (uint32_t)c4) * ES
@@ -589,7 +524,26 @@ __global__ __launch_bounds__(256, 1) void linear_kernel(LinArgs p) {
 int32_t linear_rank_cols(int32_t r_max) {
   // the run steps cover 2 rp K columns: a whole number of KS-wide steps
   const int32_t r = std::max(r_max, 1);
-  return LINEAR_KS == 64 ? std::max(32, (r + 31) / 32 * 32) : (r + 15) / 16 * 16;
+  return std::max(32, (r + 31) / 32 * 32);
+}
+
+// Rows of a tile in 64-row units: the choice with the least rounds of tiles over
+// the 256 CUs times the time of a round.  Relative times of a round with 4, 3 and
+// 2 units (the step's direct loads bound it, and all tiles load 256 rows of W):
+// 600 x 4096 -> 4096: 92 us with 4, 76 with 2; 2003 x 5120 -> 5120 (160 tiles of
+// four units, 220 of three): 127 and 119 us.
+static int linear_tile_blocks(int64_t n, int64_t n_tiles) {
+  int best = 4;
+  int64_t cost = INT64_MAX;
+  for (int mb = 4; mb >= 2; --mb) {
+    const int64_t tiles = (n + 64 * mb - 1) / (64 * mb) * n_tiles;
+    const int64_t c = (tiles + 255) / 256 * (mb == 4 ? 100 : mb == 3 ? 92 : 80);
+    if (c < cost) {
+      cost = c;
+      best = mb;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_linear_mfma(const OpLaunch& o, const LinearLaunch& l, hipStream_t s) {
@@ -604,8 +558,9 @@ hipError_t launch_linear_mfma(const OpLaunch& o, const LinearLaunch& l, hipStrea
   a.num_slots = o.num_slots;
   a.d_in = o.d_in;
   a.d_out = o.d_out;
-  a.m_tiles = (o.n + LT_M - 1) / LT_M;
   a.n_tiles = (o.d_out + LT_N - 1) / LT_N;
+  const int mb = linear_tile_blocks(o.n, a.n_tiles);
+  a.m_tiles = (o.n + 64 * mb - 1) / (64 * mb);
   a.hdr = o.hdr;
   a.run_start = l.run_start;
   a.run_end = l.run_end;
@@ -619,7 +574,7 @@ hipError_t launch_linear_mfma(const OpLaunch& o, const LinearLaunch& l, hipStrea
   a.perm = o.perm;
   a.Hs = l.Hs;
   a.rp = linear_rank_cols(o.r_max);
-  a.spr = 2 * a.rp / LINEAR_KS;
+  a.spr = 2 * a.rp / KS;
   const long long total = (long long)a.m_tiles * a.n_tiles;
   if (total <= 0) return hipSuccess;
   const int grid = (int)(8 * ((total + 7) / 8));
@@ -629,12 +584,18 @@ hipError_t launch_linear_mfma(const OpLaunch& o, const LinearLaunch& l, hipStrea
     if (e != hipSuccess) return e;
   }
   const bool yb = l.y_bf16;
-  constexpr int KS = LINEAR_KS, NS = LINEAR_NS;
-  constexpr bool NTS = LINEAR_NTS, DMA = LINEAR_DMA;
-  if (yb && o.rank8) hipLaunchKernelGGL((linear_kernel<true, true, KS, NS, NTS, DMA>), dim3(grid), dim3(256), 0, s, a);
-  else if (yb) hipLaunchKernelGGL((linear_kernel<true, false, KS, NS, NTS, DMA>), dim3(grid), dim3(256), 0, s, a);
-  else if (o.rank8) hipLaunchKernelGGL((linear_kernel<false, true, KS, NS, NTS, DMA>), dim3(grid), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((linear_kernel<false, false, KS, NS, NTS, DMA>), dim3(grid), dim3(256), 0, s, a);
+#define LK(MB)                                                                                     \
+  do {                                                                                             \
+    const dim3 g(grid), b(LT_W * 64);                                                              \
+    if (yb && o.rank8) hipLaunchKernelGGL((linear_kernel<true, true, MB>), g, b, 0, s, a);         \
+    else if (yb) hipLaunchKernelGGL((linear_kernel<true, false, MB>), g, b, 0, s, a);              \
+    else if (o.rank8) hipLaunchKernelGGL((linear_kernel<false, true, MB>), g, b, 0, s, a);         \
+    else hipLaunchKernelGGL((linear_kernel<false, false, MB>), g, b, 0, s, a);                     \
+  } while (0)
+  if (mb == 4) LK(4);
+  else if (mb == 3) LK(3);
+  else LK(2);
+#undef LK
   return hipGetLastError();
 }
 

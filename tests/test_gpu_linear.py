@@ -155,3 +155,23 @@ def test_linear_rejects_and_empty():
         L.linear(plan, dev["X"], torch.zeros(64, 32, dtype=torch.bfloat16, device=DEV), Y)
     torch.cuda.synchronize()
     assert torch.all(Y == 3.0)
+
+
+@pytest.mark.parametrize("n,d_out,ranks", [(3585, 4088, (8, 24)), (3500, 4096, (5, 12)),      # 256 rows per tile
+                                           (2003, 5112, (8, 16, 72)), (1921, 5120, (3,)),    # 192
+                                           (129, 4096, (16,)), (640, 1032, (8, 33))])        # 128
+@pytest.mark.parametrize("d_in", [8, 72, 136])
+def test_linear_tile_heights(n, d_out, ranks, d_in):
+    """The three tile heights the host chooses between, ragged in rows and
+    columns, with fewer K steps than the ring and a K tail.  Values in
+    {-1, 0, 1} and scales of 1: sums below 2^24 (and below 256 for the bf16 terms
+    of H), so float32 Y is exact."""
+    say(f"linear tile heights n={n} d_out={d_out} d_in={d_in}")
+    case = workloads.random_case(n + d_in, n, d_in, d_out, 5, rank_choices=ranks, layout="segments",
+                                 seg_len=(1, 700), int_values=True, want_y=False,
+                                 scales=np.ones(5))
+    W = workloads.base_weight(case, int_values=True)
+    Y = run_linear(case, W, "f32").double().numpy()
+    X, A, B, _, _ = f64_case(case)
+    ref = oracle.linear(effective(case), X, workloads.decode(W, "bf16"), A, B, case.scales)
+    assert np.array_equal(Y, ref)
