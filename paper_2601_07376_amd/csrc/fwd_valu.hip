@@ -1,8 +1,24 @@
-// Forward kernels on the vector ALU for any mix of float32 / bfloat16 storage
-// (Section 3.4, LoRA layer equation).  Every dot product is a sequential
-// float32 fused multiply-add chain in index order, one thread per output, so
-// the result does not depend on the launch shape; the operands come from LDS.
+// Forward kernels for any mix of float32 / bfloat16 storage with a float32
+// operand (Section 3.4, LoRA layer equation), on the float32 matrix-core
+// instruction v_mfma_f32_16x16x4_f32: float32 products and sums, fixed
+// summation order.
+//
+// Matrix core: lane l holds row l % 16 of the A operand and column l % 16 of the B
+// operand at K index l / 16; the accumulator lane l holds rows 4 (l / 16) + v of
+// column l % 16.  A lane loads four consecutive K values at K offset 4 (l / 16) of
+// a 16-wide K step and feeds one of them to each of four instructions: any
+// assignment of K values to instructions gives the same sum as long as both
+// operands use it.
+//
+// What bounds them: latency.  With one thread per output and operands staged in
+// LDS, a unit's sums were one chain of d_in fused multiply-adds and every row
+// group of a short batch had a few busy waves; here eight waves share K.
+// Whole float32 lora_apply calls, before and now: 64 rows 256 -> 256 rank 8 13.5
+// and 11.4 us; 200 rows 1024 -> 1024 rank 16 45 and 16; 2000 rows 4096 -> 4096 rank 16
+// 261 and 97, rank 128 1897 and 486.  The error against 64 bits fell from 1.0e-6 to
+// 0.4e-6 (eight shorter sums instead of one chain of 4096).
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "lora_internal.h"
@@ -11,10 +27,26 @@ namespace lora {
 
 namespace {
 
+typedef f32x4 v4;
+
+// Four consecutive values as float32 (16-byte aligned float32, 8-byte bfloat16).
+template <bool BF16>
+__device__ __forceinline__ v4 ld4(const void* p, int64_t i) {
+  if (BF16) {
+    const uint2 u = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(p) + i);
+    return v4{bf16_to_f32(u.x & 0xffffu), bf16_to_f32(u.x >> 16), bf16_to_f32(u.y & 0xffffu),
+              bf16_to_f32(u.y >> 16)};
+  }
+  return *reinterpret_cast<const v4*>(reinterpret_cast<const float*>(p) + i);
+}
 template <bool BF16>
 __device__ __forceinline__ float ld(const void* p, int64_t i) {
   if (BF16) return bf16_to_f32(reinterpret_cast<const uint16_t*>(p)[i]);
   return reinterpret_cast<const float*>(p)[i];
+}
+// (not a template: the host pass cannot resolve the builtin inside one)
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 struct ValuArgs {
@@ -34,24 +66,19 @@ struct ValuArgs {
   int32_t n_rows;           // rows of the batch: the bound of every row id read from the plan
 };
 
-// Work unit: an entry's rows in groups of VG; each group's operands are staged
-// in LDS (the next chunk's loads in flight while a chunk is used), so the
-// per-thread chains read LDS, not memory.
-constexpr int VG = 16;                 // rows per unit
+// Work unit: an entry's rows in groups of VG (one matrix-core tile).
+constexpr int VG = 16;
 constexpr int VGROUPS = RB_ROWS / VG;  // most row groups of an entry
+constexpr int VW = 8;                  // waves of the shrink
 
-// H[t, j] = sum_k X[t, k] A[j, k] for ranks up to RM, k staged in chunks of
-// VK (fewer, longer chunks for small ranks).  Thread pairs (row, j) = tid + 256 m.
-template <bool XB, bool WB, int RM>
-__global__ __launch_bounds__(256) void shrink_valu_kernel(ValuArgs p) {
-  constexpr int VK = RM <= 32 ? 256 : 64;
-  constexpr int PM = VG * RM / 256;                     // pairs per thread
-  constexpr int XL = VG * VK / 256;                     // X values per thread and chunk
-  constexpr int AL = RM * VK / 256;                     // A values per thread and chunk
-  constexpr int KS = VK + 4;                            // LDS row stride (16-byte rows)
-  __shared__ __align__(16) float s_x[VG][KS];
-  __shared__ __align__(16) float s_a[RM][KS];
-  const int tid = threadIdx.x;
+// H[t, j] = sum_k X[t, k] A[j, k], ranks up to 16 NT: wave w takes the K steps
+// w, w + 8, ..., two per batch, double buffered; the waves' sums meet in LDS.
+template <bool XB, bool WB, int NT>
+__global__ __launch_bounds__(VW * 64) void shrink_valu_kernel(ValuArgs p) {
+  constexpr int U = NT <= 2 ? 2 : 1;
+  __shared__ f32x4 s_red[VW * NT * 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_id();
+  const int n = lane & 15, kg = (lane >> 4) * 4;
   const int first = p.first_word >= 0 ? p.hdr[p.first_word] : 0;
   const int count = p.hdr[p.count_word] - first;
   for (int tile = blockIdx.x; tile < count * VGROUPS; tile += gridDim.x) {
@@ -61,133 +88,148 @@ __global__ __launch_bounds__(256) void shrink_valu_kernel(ValuArgs p) {
     if (rows <= 0) continue;
     const Slot m = load_slot(p.meta, a);
     const int r = m.rank;
-    int xt[XL];
+    if (r <= 0) continue;
+    const int64_t xo = (int64_t)ck_row(p.hdr, p.perm[p0 + min(n, rows - 1)], p.n_rows) * p.ldx;
+    int64_t ao[NT];
 #pragma unroll
-    for (int u = 0; u < XL; ++u) {
-      const int i = (tid + 256 * u) / VK;
-      xt[u] = ck_row(p.hdr, p.perm[p0 + (i < rows ? i : rows - 1)], p.n_rows);
-    }
-    float xv[XL], av[AL];
-    auto fetch = [&](int k0) {
+    for (int nt = 0; nt < NT; ++nt) ao[nt] = (int64_t)min(nt * 16 + n, r - 1) * p.d_in;
+    struct Buf {
+      v4 x[U], a[U][NT];
+    };
+    auto load = [&](Buf& b, int bt) {
 #pragma unroll
-      for (int u = 0; u < XL; ++u) {
-        const int k = k0 + (tid + 256 * u) % VK;
-        xv[u] = k < p.d_in ? ld<XB>(p.X, (int64_t)xt[u] * p.ldx + k) : 0.0f;
-      }
+      for (int u = 0; u < U; ++u) {
+        const int k = (bt * VW * U + w * U + u) * 16 + kg, kk = min(k, p.d_in - 4);
+        b.x[u] = ld4<XB>(p.X, xo + kk);
 #pragma unroll
-      for (int u = 0; u < AL; ++u) {
-        const int q = tid + 256 * u, j = q / VK, k = k0 + q % VK;
-        av[u] = (j < r && k < p.d_in) ? ld<WB>(m.A, (int64_t)j * p.d_in + k) : 0.0f;
+        for (int nt = 0; nt < NT; ++nt) b.a[u][nt] = ld4<WB>(m.A, ao[nt] + kk);
       }
     };
-    float acc[PM];
+    f32x4 acc[NT];
 #pragma unroll
-    for (int i = 0; i < PM; ++i) acc[i] = 0.0f;
-    fetch(0);
-    for (int k0 = 0; k0 < p.d_in; k0 += VK) {
-      __syncthreads();                 // the previous chunk's reads are done
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](const Buf& b, int bt) {
 #pragma unroll
-      for (int u = 0; u < XL; ++u) s_x[(tid + 256 * u) / VK][(tid + 256 * u) % VK] = xv[u];
+      for (int u = 0; u < U; ++u) {
+        const bool kv = (bt * VW * U + w * U + u) * 16 + kg < p.d_in;   // d_in is a multiple of 8
 #pragma unroll
-      for (int u = 0; u < AL; ++u) s_a[(tid + 256 * u) / VK][(tid + 256 * u) % VK] = av[u];
-      __syncthreads();
-      if (k0 + VK < p.d_in) fetch(k0 + VK);
-      const int kn = min(VK, p.d_in - k0);
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int mm = 0; mm < PM; ++mm) {
-        const int q = tid + 256 * mm, i = q / max(r, 1), j = q - i * max(r, 1);
-        if (r == 0 || i >= rows) continue;
-        // kn is a multiple of 8 (so is every dimension)
-        float c = acc[mm];
-#pragma unroll 8
-        for (int kk = 0; kk < kn; kk += 4) {
-          const float4 x4 = *reinterpret_cast<const float4*>(&s_x[i][kk]);
-          const float4 a4 = *reinterpret_cast<const float4*>(&s_a[j][kk]);
-          c = fmaf(x4.x, a4.x, c);
-          c = fmaf(x4.y, a4.y, c);
-          c = fmaf(x4.z, a4.z, c);
-          c = fmaf(x4.w, a4.w, c);
-        }
-        acc[mm] = c;
+          for (int c = 0; c < 4; ++c)
+            // (both operands zeroed: an infinity in the clamped values times 0 is not 0)
+            acc[nt] = mfma_f32(kv ? b.x[u][c] : 0.0f, kv ? b.a[u][nt][c] : 0.0f, acc[nt]);
       }
+    };
+    const int nb = (p.d_in + VW * U * 16 - 1) / (VW * U * 16);
+    Buf b0, b1;
+    load(b0, 0);
+    for (int bt = 0; bt < nb; bt += 2) {      // (batches past the end add zeros)
+      load(b1, bt + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(b0, bt);
+      load(b0, bt + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(b1, bt + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 7");
+      __builtin_amdgcn_sched_barrier(0);
     }
+    mfma_fence();
+    __syncthreads();                          // the previous unit's reads of s_red are done
 #pragma unroll
-    for (int mm = 0; mm < PM; ++mm) {
-      const int q = tid + 256 * mm, i = q / max(r, 1), j = q - i * max(r, 1);
-      if (r == 0 || i >= rows) continue;
-      p.H[(int64_t)ck_row(p.hdr, p.perm[p0 + i], p.n_rows) * p.ldh + j] = acc[mm];
+    for (int nt = 0; nt < NT; ++nt) s_red[(w * NT + nt) * 64 + lane] = acc[nt];
+    __syncthreads();
+    for (int q = tid; q < NT * 64; q += VW * 64) {
+      f32x4 v[VW];
+#pragma unroll
+      for (int k = 0; k < VW; ++k) v[k] = s_red[k * NT * 64 + q];
+      const f32x4 s = ((v[0] + v[4]) + (v[2] + v[6])) + ((v[1] + v[5]) + (v[3] + v[7]));
+      const int j = (q >> 6) * 16 + (q & 15), i0 = ((q & 63) >> 4) * 4;
+      if (j >= r) continue;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k < rows)
+          p.H[(int64_t)ck_row(p.hdr, p.perm[p0 + i0 + k], p.n_rows) * p.ldh + j] = s[k];
     }
   }
 }
 
-// Y[t, o] += s * sum_j H[t, j] B[o, j]; unit = (entry, 256 columns, row group),
-// thread = column, the group's H rows staged in LDS.
-template <bool WB, bool YB>
+// Y[t, o] += s * sum_j H[t, j] B[o, j]; unit = (entry, 256 columns, row group), 64
+// columns per wave.  B is the A operand, so a lane ends with four consecutive
+// columns of one row.  NT: rank tiles of 16.
+template <bool WB, bool YB, int NT>
 __global__ __launch_bounds__(256) void expand_valu_kernel(ValuArgs p) {
-  constexpr int HL = VG * LORA_MAX_RANK / 256;          // H values per thread
-  constexpr int JB = 32;                                // B values per thread in flight
-  __shared__ float s_h[VG][LORA_MAX_RANK];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int n = lane & 15, g4 = (lane >> 4) * 4;
   const int first = p.first_word >= 0 ? p.hdr[p.first_word] : 0;
   const int count = p.hdr[p.count_word] - first;
   const int n_ot = (p.d_out + 255) / 256;
   for (int tile = blockIdx.x; tile < count * n_ot * VGROUPS; tile += gridDim.x) {
     const int g = tile % VGROUPS, eo = tile / VGROUPS;
-    const int e = eo / n_ot, o = (eo - e * n_ot) * 256 + tid;
+    const int e = eo / n_ot, o0 = (eo - e * n_ot) * 256 + w * 64;
     const int4 en = load_entry(p.rb, first + e);
     const int a = ck_slot(p.hdr, en.x, p.num_slots), rows = min(VG, en.z - g * VG), p0 = en.y + g * VG;
     if (rows <= 0) continue;
     const Slot m = load_slot(p.meta, a);
     const int r = m.rank;
     const float s = m.scale;
-    // B (first JB ranks) and Y of this thread's column are requested together
-    // with H, so the unit costs one round trip after the slot
-    const bool ov = o < p.d_out;
-    const int oc = ov ? o : p.d_out - 1;
-    int yt[VG];
-    float yv[VG];
+    if (r <= 0) continue;
+    const bool r4 = (r & 3) == 0;
+    const int t = ck_row(p.hdr, p.perm[p0 + min(n, rows - 1)], p.n_rows);
+    // Y of the lane's columns and the first B tile are requested together with H
+    v4 y[4];
 #pragma unroll
-    for (int i = 0; i < VG; ++i) {
-      yt[i] = ck_row(p.hdr, p.perm[p0 + (i < rows ? i : rows - 1)], p.n_rows);
-      const int64_t yo = (int64_t)yt[i] * p.ldy + oc;
-      yv[i] = YB ? bf16_to_f32(reinterpret_cast<const uint16_t*>(p.Y)[yo])
-                 : reinterpret_cast<const float*>(p.Y)[yo];
-    }
-    float b[JB];
-    auto fetch_b = [&](int j0) {
+    for (int c = 0; c < 4; ++c)
+      y[c] = ld4<YB>(p.Y, (int64_t)t * p.ldy + min(o0 + c * 16 + g4, p.d_out - 4));
+    f32x4 acc[4];
 #pragma unroll
-      for (int jj = 0; jj < JB; ++jj)
-        b[jj] = j0 + jj < r ? ld<WB>(m.B, (int64_t)oc * r + j0 + jj) : 0.0f;
-    };
-    fetch_b(0);
-    __syncthreads();                   // the previous unit's reads of s_h are done
+    for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // four values of a row from rank column j on, zero past the rank
+    auto rank4 = [&](auto b16, const void* q, int64_t row, int j, bool vec) {
+      constexpr bool B16 = decltype(b16)::value;
+      v4 v;
+      if (vec) {
+        v = ld4<B16>(q, row + min(j, r - 4));
 #pragma unroll
-    for (int u = 0; u < HL; ++u) {
-      const int q = tid + 256 * u, i = q / LORA_MAX_RANK, j = q % LORA_MAX_RANK;
-      s_h[i][j] = (i < rows && j < r) ? p.H[(int64_t)ck_row(p.hdr, p.perm[p0 + i], p.n_rows) * p.ldh + j] : 0.0f;
-    }
-    __syncthreads();
-    float acc[VG];
+        for (int c = 0; c < 4; ++c) v[c] = j < r ? v[c] : 0.0f;
+      } else {
 #pragma unroll
-    for (int i = 0; i < VG; ++i) acc[i] = 0.0f;
-    for (int j0 = 0; j0 < r; j0 += JB) {
-      if (j0 > 0) fetch_b(j0);
-      const int jn = min(JB, r - j0);
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) {
-        if (jj >= jn) break;
-#pragma unroll
-        for (int i = 0; i < VG; ++i) acc[i] = fmaf(s_h[i][j0 + jj], b[jj], acc[i]);
+        for (int c = 0; c < 4; ++c) {
+          const float x = ld<B16>(q, row + min(j + c, r - 1));
+          v[c] = j + c < r ? x : 0.0f;
+        }
       }
-    }
-    if (!ov) continue;
+      return v;
+    };
+    v4 h[NT], b[NT][4];
 #pragma unroll
-    for (int i = 0; i < VG; ++i) {
-      if (i >= rows) break;
-      const int64_t yo = (int64_t)yt[i] * p.ldy + o;
-      const float y = fmaf(s, acc[i], yv[i]);
-      if (YB) reinterpret_cast<uint16_t*>(p.Y)[yo] = (uint16_t)f32_to_bf16_rne(y);
-      else reinterpret_cast<float*>(p.Y)[yo] = y;
+    for (int nt = 0; nt < NT; ++nt) {
+      const int j = nt * 16 + g4;
+      h[nt] = rank4(std::integral_constant<bool, false>{}, p.H, (int64_t)t * p.ldh, j, r4);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        b[nt][c] = rank4(std::integral_constant<bool, WB>{}, m.B,
+                         (int64_t)min(o0 + c * 16 + n, p.d_out - 1) * r, j, r4);
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[c] = mfma_f32(b[nt][c][k], h[nt][k], acc[c]);
+    mfma_fence();
+    if (n >= rows) continue;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int o = o0 + c * 16 + g4;
+      if (o >= p.d_out) continue;             // d_out is a multiple of 8
+      v4 v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = fmaf(s, acc[c][k], y[c][k]);
+      const int64_t yo = (int64_t)t * p.ldy + o;
+      if (YB) *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.Y) + yo) =
+          make_uint2(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]));
+      else *reinterpret_cast<v4*>(reinterpret_cast<float*>(p.Y) + yo) = v;
     }
   }
 }
@@ -219,18 +261,20 @@ hipError_t launch_shrink_valu(const OpLaunch& o, const void* X, lora_dtype x_dty
   a.ldh = ldh;
   const int grid = (int)std::max<long long>(1, std::min<long long>((long long)o.rb_ub * VGROUPS, 4096));
   const bool xb = x_dtype == LORA_BF16, wb = w_dtype == LORA_BF16;
-  if (o.r_max <= 32) {
-    if (xb && wb) hipLaunchKernelGGL((shrink_valu_kernel<true, true, 32>), dim3(grid), dim3(256), 0, s, a);
-    else if (xb) hipLaunchKernelGGL((shrink_valu_kernel<true, false, 32>), dim3(grid), dim3(256), 0, s, a);
-    else if (wb) hipLaunchKernelGGL((shrink_valu_kernel<false, true, 32>), dim3(grid), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((shrink_valu_kernel<false, false, 32>), dim3(grid), dim3(256), 0, s, a);
-  } else {
-    constexpr int R = LORA_MAX_RANK;
-    if (xb && wb) hipLaunchKernelGGL((shrink_valu_kernel<true, true, R>), dim3(grid), dim3(256), 0, s, a);
-    else if (xb) hipLaunchKernelGGL((shrink_valu_kernel<true, false, R>), dim3(grid), dim3(256), 0, s, a);
-    else if (wb) hipLaunchKernelGGL((shrink_valu_kernel<false, true, R>), dim3(grid), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((shrink_valu_kernel<false, false, R>), dim3(grid), dim3(256), 0, s, a);
-  }
+  const int nt = (o.r_max + 15) / 16;
+#define SV(NT)                                                                                         \
+  do {                                                                                                 \
+    const dim3 g(grid), b(VW * 64);                                                                    \
+    if (xb && wb) hipLaunchKernelGGL((shrink_valu_kernel<true, true, NT>), g, b, 0, s, a);             \
+    else if (xb) hipLaunchKernelGGL((shrink_valu_kernel<true, false, NT>), g, b, 0, s, a);             \
+    else if (wb) hipLaunchKernelGGL((shrink_valu_kernel<false, true, NT>), g, b, 0, s, a);             \
+    else hipLaunchKernelGGL((shrink_valu_kernel<false, false, NT>), g, b, 0, s, a);                    \
+  } while (0)
+  if (nt <= 1) SV(1);
+  else if (nt <= 2) SV(2);
+  else if (nt <= 4) SV(4);
+  else SV(8);
+#undef SV
   return hipGetLastError();
 }
 
@@ -245,10 +289,20 @@ hipError_t launch_expand_valu(const OpLaunch& o, const float* H, int64_t ldh,
   const long long tiles = (long long)o.rb_ub * ((o.d_out + 255) / 256) * VGROUPS;
   const int grid = (int)std::max<long long>(1, std::min<long long>(tiles, 8192));
   const bool wb = w_dtype == LORA_BF16, yb = y_dtype == LORA_BF16;
-  if (wb && yb) hipLaunchKernelGGL((expand_valu_kernel<true, true>), dim3(grid), dim3(256), 0, s, a);
-  else if (wb) hipLaunchKernelGGL((expand_valu_kernel<true, false>), dim3(grid), dim3(256), 0, s, a);
-  else if (yb) hipLaunchKernelGGL((expand_valu_kernel<false, true>), dim3(grid), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((expand_valu_kernel<false, false>), dim3(grid), dim3(256), 0, s, a);
+  const int nt = (o.r_max + 15) / 16;
+#define EV(NT)                                                                                         \
+  do {                                                                                                 \
+    const dim3 g(grid), b(256);                                                                        \
+    if (wb && yb) hipLaunchKernelGGL((expand_valu_kernel<true, true, NT>), g, b, 0, s, a);             \
+    else if (wb) hipLaunchKernelGGL((expand_valu_kernel<true, false, NT>), g, b, 0, s, a);             \
+    else if (yb) hipLaunchKernelGGL((expand_valu_kernel<false, true, NT>), g, b, 0, s, a);             \
+    else hipLaunchKernelGGL((expand_valu_kernel<false, false, NT>), g, b, 0, s, a);                    \
+  } while (0)
+  if (nt <= 1) EV(1);
+  else if (nt <= 2) EV(2);
+  else if (nt <= 4) EV(4);
+  else EV(8);
+#undef EV
   return hipGetLastError();
 }
 

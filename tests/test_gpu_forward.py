@@ -353,3 +353,40 @@ def test_shrink_row_products(n, d_in):
             assert np.array_equal(H[t, :r], X[t] @ A[a].T), f"slot {a}"
             assert np.all(H[t, r:] == 7.0), "columns past the rank were written"
         assert np.all(H[case.idx < 0] == 7.0), "rows with no adapter were written"
+
+
+@pytest.mark.parametrize("xdt,wdt,ydt", [("f32", "f32", "f32"), ("bf16", "f32", "f32"),
+                                         ("f32", "bf16", "bf16")])
+@pytest.mark.parametrize("d_in,d_out", [(8, 8), (24, 264), (264, 1032), (1160, 72)])
+def test_apply_float32_matrix_core(xdt, wdt, ydt, d_in, d_out):
+    """The float32 path at the edges of its tiles: ranks of every residue mod 4
+    and of one to eight tiles, row groups around 16, K shorter and longer than a
+    batch of the eight waves, ragged columns.  Values in {-1, 0, 1}, |H| <= 1160,
+    |Y| < 2^24 and scales of 1: exact in float32 (bf16 Y: rounded once)."""
+    say(f"float32 path {xdt} {wdt} {ydt} {d_in} -> {d_out}")
+    ranks = [1, 2, 3, 4, 8, 17, 32, 33, 66, 128]
+    case = workloads.random_case(d_in + d_out, 700, d_in, d_out, len(ranks), ranks=ranks,
+                                 layout="segments", seg_len=(1, 70), int_values=True, x_dtype=xdt,
+                                 w_dtype=wdt, y_dtype=ydt, scales=np.ones(len(ranks)))
+    got, _ = run_apply(case)
+    X, A, B, Y, _ = f64_case(case)
+    ref = oracle.apply(effective(case), X, Y, A, B, case.scales)
+    assert np.array_equal(workloads.decode(got, ydt), workloads.decode(workloads.encode(ref, ydt), ydt))
+
+
+def test_apply_float32_infinities_stay_in_their_rows():
+    """Clamped loads past a row's end, its rank or its group bring values of
+    other positions: an infinity there must not reach a finite row."""
+    say("float32 path infinities")
+    case = workloads.random_case(5, 90, 24, 40, 3, ranks=[3, 8, 20], layout="segments",
+                                 seg_len=(1, 30), int_values=True, x_dtype="f32", w_dtype="f32",
+                                 y_dtype="f32", frac_none=0.0, scales=np.ones(3))
+    dev = case_to_device(case, DEV)
+    bad = [0, 17, 41, 89]
+    dev["X"][bad, -4:] = float("inf")
+    plan = make_plan(case, dev, make_table(case, dev), mask=False)
+    Y = L.apply(plan, dev["X"], dev["Y"].clone()).cpu().double().numpy()
+    X, A, B, Y0, _ = f64_case(case)
+    ref = oracle.apply(effective(case), X, Y0, A, B, case.scales)
+    good = np.setdiff1d(np.arange(90), bad)
+    assert np.array_equal(Y[good], ref[good])
