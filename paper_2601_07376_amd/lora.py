@@ -11,7 +11,9 @@ each op's buffers, bounds checks of plan values in the kernels); tables and
 plans of the two libraries do not mix.
 """
 import ctypes
+import operator
 import os
+import struct
 
 import numpy as np
 import torch
@@ -116,14 +118,22 @@ def _dtype(t):
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
+# Pointers go as plain integers (every prototype says void*), and the current
+# stream's handle is read without building a Stream object: together about 4 us
+# of a plan + apply of a small batch.
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _used_on(stream, *tensors):
@@ -457,7 +467,49 @@ def adamw_step(params, stream=None):
     rounded update), and ``step``, ``lr``, ``beta1``, ``beta2``, ``eps``,
     ``weight_decay``.  Tensors are passed as flat arrays, so they must be
     contiguous."""
-    recs = (AdamWTensor * max(len(params), 1))()
+    recs = _adamw_records(params)
+    _check(lib().lora_adamw_step(ctypes.cast(recs, ctypes.c_void_p), len(params), _stream(stream)))
+
+
+_F32_KEYS = operator.itemgetter("p", "m", "v", "g")
+_HYPER = operator.itemgetter("step", "lr", "beta1", "beta2", "eps", "weight_decay")
+_DTYPE = operator.attrgetter("dtype")
+_RECORD = "PPPPPqi5f"      # lora_adamw_tensor, field by field
+
+
+def _adamw_records(params):
+    """The array of lora_adamw_tensor records.  Dozens of small tensors step at
+    once, so their checks and fields are collected list by list (16 tensors:
+    21 us against 32 record by record); anything out of the ordinary is left to
+    the record-by-record code, which names it."""
+    n_rec = len(params)
+    recs = (AdamWTensor * max(n_rec, 1))()
+    T = torch.Tensor
+    try:
+        f32, half, hyper = [], [], []
+        for q in params:
+            f32 += _F32_KEYS(q)
+            half.append(q.get("p_bf16"))
+            hyper.append(_HYPER(q))
+        sizes = list(map(T.numel, f32))
+        n = sizes[::4]
+        given = [t for t in half if t is not None]
+        if (sizes[1::4] == n and sizes[2::4] == n and sizes[3::4] == n
+                and set(map(_DTYPE, f32)) <= {torch.float32}
+                and set(map(_DTYPE, given)) <= {torch.bfloat16}
+                and all(map(T.is_contiguous, f32)) and all(map(T.is_contiguous, given))
+                and all(t is None or t.numel() == k for t, k in zip(half, n))):
+            ptrs = list(map(T.data_ptr, f32))
+            fields = []
+            for i in range(n_rec):
+                fields += ptrs[4 * i:4 * i + 4]
+                fields.append(0 if half[i] is None else half[i].data_ptr())
+                fields.append(n[i])
+                fields += hyper[i]
+            struct.pack_into("@" + _RECORD * n_rec, recs, 0, *fields)
+            return recs
+    except (AttributeError, KeyError, TypeError, OverflowError, struct.error):
+        pass
     for i, q in enumerate(params):
         n = q["p"].numel()
         for k in ("p", "m", "v", "g"):
@@ -471,7 +523,7 @@ def adamw_step(params, stream=None):
                               q["g"].data_ptr(), pb.data_ptr() if pb is not None else None, n,
                               int(q["step"]), float(q["lr"]), float(q["beta1"]),
                               float(q["beta2"]), float(q["eps"]), float(q["weight_decay"]))
-    _check(lib().lora_adamw_step(ctypes.cast(recs, ctypes.c_void_p), len(params), _stream(stream)))
+    return recs
 
 
 LOSS_CE, LOSS_IS, LOSS_PPO = 0, 1, 2
