@@ -66,7 +66,7 @@ struct Vec {
 
 // 16 bytes of a gradient row.  Rows whose logits are read twice (too long for the
 // registers) write past the caches, which leaves the logits in them for the
-// second read: 2000 x 100003 bf16 216 -> 190 us, 4000 x 32000 float32 157 -> 145.
+// second read: 2000 x 100003 bf16 216 -> 197 us, 4000 x 32000 float32 157 -> 149.
 // Rows read once are better off with plain stores: 8192 x 32768 bf16, 30 % active,
 // 154 against 158.
 template <bool NT>
@@ -76,8 +76,8 @@ __device__ __forceinline__ void st16(void* p, uint4 v) {
   else *reinterpret_cast<u32x4*>(p) = x;
 }
 
-// RES: a row's logits fit the workgroup's registers (they are read once).
-template <bool ZB, bool DB, bool RES>
+// NT: the rows are too long for the workgroup's registers (see st16).
+template <bool ZB, bool DB, bool NT>
 __global__ __launch_bounds__(LS_THREADS) void token_loss_kernel(LossArgs a) {
   constexpr int E = Vec<ZB>::E;
   constexpr int ES = ZB ? 2 : 4, DS = DB ? 2 : 4;
@@ -105,11 +105,11 @@ __global__ __launch_bounds__(LS_THREADS) void token_loss_kernel(LossArgs a) {
     for (int q = tid; q < nvec; q += LS_THREADS) {
       const int v0 = q * E;
       if (v0 + E <= V) {
-        if (DB && E == 8) st16<!RES>(drow + (int64_t)v0 * DS, make_uint4(0, 0, 0, 0));
+        if (DB && E == 8) st16<NT>(drow + (int64_t)v0 * DS, make_uint4(0, 0, 0, 0));
         else if (DB) *reinterpret_cast<uint2*>(drow + (int64_t)v0 * DS) = make_uint2(0, 0);
         else {
           for (int h = 0; h < E / 4; ++h)
-            st16<!RES>(drow + (int64_t)(v0 + 4 * h) * DS, make_uint4(0, 0, 0, 0));
+            st16<NT>(drow + (int64_t)(v0 + 4 * h) * DS, make_uint4(0, 0, 0, 0));
         }
       } else {
         for (int i = v0; i < V; ++i) {
@@ -132,9 +132,10 @@ __global__ __launch_bounds__(LS_THREADS) void token_loss_kernel(LossArgs a) {
                                : reinterpret_cast<const float*>(zrow)[y];
 
   // pass 1: running (max, sum) per thread over its vectors q = tid + 256 k
+  const bool resident = nvec <= LS_NV * LS_THREADS;
   Vec<ZB> reg[LS_NV];
   float m = -INFINITY, s = 0.f;
-  for (int q0 = 0; q0 < (RES ? 1 : nvec); q0 += LS_NV * LS_THREADS) {
+  for (int q0 = 0; q0 < nvec; q0 += LS_NV * LS_THREADS) {
 #pragma unroll
     for (int k = 0; k < LS_NV; ++k) {
       const int q = q0 + tid + k * LS_THREADS;
@@ -207,8 +208,8 @@ __global__ __launch_bounds__(LS_THREADS) void token_loss_kernel(LossArgs a) {
   const float g = s_g;
 
   // pass 2: g (exp(z - lse) - [v == y]) for every element
-  for (int q0 = 0; q0 < (RES ? 1 : nvec); q0 += LS_NV * LS_THREADS) {
-    if (!RES) {
+  for (int q0 = 0; q0 < nvec; q0 += LS_NV * LS_THREADS) {
+    if (!resident) {
 #pragma unroll
       for (int k = 0; k < LS_NV; ++k) {
         const int q = q0 + tid + k * LS_THREADS;
@@ -231,12 +232,12 @@ __global__ __launch_bounds__(LS_THREADS) void token_loss_kernel(LossArgs a) {
           uint32_t o[E / 2];
 #pragma unroll
           for (int i = 0; i < E / 2; ++i) o[i] = pack2_bf16(d[2 * i], d[2 * i + 1]);
-          if (E == 8) st16<!RES>(drow + (int64_t)v0 * DS, make_uint4(o[0], o[1], o[2], o[3]));
+          if (E == 8) st16<NT>(drow + (int64_t)v0 * DS, make_uint4(o[0], o[1], o[2], o[3]));
           else *reinterpret_cast<uint2*>(drow + (int64_t)v0 * DS) = make_uint2(o[0], o[1]);
         } else {
 #pragma unroll
           for (int h = 0; h < E / 4; ++h)
-            st16<!RES>(drow + (int64_t)(v0 + 4 * h) * DS,
+            st16<NT>(drow + (int64_t)(v0 + 4 * h) * DS,
                  make_uint4(__float_as_uint(d[4 * h]), __float_as_uint(d[4 * h + 1]),
                             __float_as_uint(d[4 * h + 2]), __float_as_uint(d[4 * h + 3])));
         }
@@ -277,8 +278,8 @@ hipError_t launch_token_loss(const LossLaunch& l, hipStream_t s) {
   const bool res = (l.vocab + per - 1) / per <= LS_NV * LS_THREADS;
 #define LS(Z, D)                                                                               \
   do {                                                                                         \
-    if (res) hipLaunchKernelGGL((token_loss_kernel<Z, D, true>), grid, block, 0, s, a);        \
-    else hipLaunchKernelGGL((token_loss_kernel<Z, D, false>), grid, block, 0, s, a);           \
+    if (res) hipLaunchKernelGGL((token_loss_kernel<Z, D, false>), grid, block, 0, s, a);       \
+    else hipLaunchKernelGGL((token_loss_kernel<Z, D, true>), grid, block, 0, s, a);            \
   } while (0)
   if (l.logits_bf16 && l.dlogits_bf16) LS(true, true);
   else if (l.logits_bf16) LS(true, false);
