@@ -378,9 +378,7 @@ lora_status lora_grad_x(const lora_plan* p, const void* dY, lora_dtype dy_dtype,
 /* Both gradients of one backward step in one call: lora_grad's dA_a / dB_a
  * and lora_grad_x's dX, with exactly their results (same kernels, same
  * arguments and semantics as the two calls).  G = dY B_a is computed once for
- * both; then dX is written on a library-owned second stream of the stream's
- * device, forked from and joined back into `stream` with events, beside the
- * adapter gradients' reduction over rows.  ws:
+ * both.  Everything runs on `stream`.  ws:
  * lora_backward_workspace_bytes(p) bytes, 16-byte aligned.  Needs bfloat16 dY
  * and weights (the input gradient's matrix-core path).  Errors: those of the
  * two calls, all checked before anything is enqueued. */

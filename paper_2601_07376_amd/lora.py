@@ -427,7 +427,7 @@ def backward_workspace(plan):
 def backward(plan, X, dY, dX, dA=None, dB=None, H_saved=None, accumulate=False, ws=None,
              stream=None):
     """grad and grad_x of one backward step in one call (the input gradient
-    beside the adapter gradients); returns (dA, dB, dX)."""
+    after the adapter gradients, the row products once for both); returns (dA, dB, dX)."""
     t = plan.table
     if dA is None:
         dA = [torch.empty(r, t.d_in, dtype=torch.float32, device=X.device) if r > 0 else None
