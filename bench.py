@@ -681,20 +681,18 @@ HEADLINE_KERNELS = ("ids_shrink_kernel", "ids_expand_kernel")
 # kernels of one call of each measured op, per workload (each launched once per
 # call; names as the counter summary prints them)
 OP_KERNELS = {
-    ("tiny_sgmv_fp32", "lora_apply"): ("shrink_valu_kernel<false, false, 32>(ValuArgs)",
-                                        "expand_valu_kernel<false, false>(ValuArgs)"),
+    ("tiny_sgmv_fp32", "lora_apply"): ("shrink_valu_kernel<false, false, 1>(ValuArgs)",
+                                        "expand_valu_kernel<false, false, 1>(ValuArgs)"),
     ("decode_bgmv", "lora_apply_ids"): ("ids_shrink_kernel<1, 8>", "ids_expand_kernel<true, 1, true>"),
     ("prefill_sgmv", "lora_apply"): ("shrink_kernel<4, 1>", "expand_kernel<true, true, 2, 1>"),
     ("prefill_sgmv", "lora_linear"): ("shrink_kernel<4, 1>", "linear_hpack_kernel(LinArgs)",
-                                      "linear_kernel<true, true, 64, 2, true, true>(LinArgs)"),
-    ("skewed_hetero", "lora_apply"): ("shrink_fine_kernel<4, false>",
+                                      "linear_kernel<true, true, 4>(LinArgs)"),
+    ("skewed_hetero", "lora_apply"): ("shrink_fine_kernel<4>",
                                       "expand_fine_kernel<true, true, 2, 2, false>",
                                       "small_shrink_kernel<4, 2>", "small_expand_kernel<true, 4, true>"),
-    ("masked_backward", "lora_grad"): ("hg_kernel<2>(GradArgs)", "hgsum_kernel(GradArgs)",
-                                       "dadb_kernel<2>(GradArgs)"),
-    ("masked_backward", "lora_grad_x"): ("shrink_fine_kernel<2, true>",
-                                         "expand_fine_kernel<false, true, 1, 1, true>"),
-    ("masked_backward", "lora_token_loss"): ("token_loss_kernel<true, true>(LossArgs)",),
+    # (lora_grad and lora_grad_x share rowprod_kernel, with and without H: its mean
+    # over both says nothing about either call)
+    ("masked_backward", "lora_token_loss"): ("token_loss_kernel<true, true, false>(LossArgs)",),
     ("masked_backward", "lora_adamw_step"): ("adamw_kernel(AdamArgs)",),
 }
 # the calibration copy (torch's elementwise negation of 1 GiB float32 into a new
